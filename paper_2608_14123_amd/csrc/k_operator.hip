@@ -1,15 +1,13 @@
 // K1: sum-factorised SIPG operator apply / residual on curvilinear hexahedra
 // (eq. helmholtz:dgm) and the one-time geometry kernels (Sec. 2.2).
 //
-// One workgroup takes EPB elements, one thread per node.  The element's u and
-// the contravariant fluxes F_b = sum_c G_bc d_c u (G_bc = w J nu grad xi_b .
-// grad xi_c) live in LDS.  Face terms use the identity
+// Face terms use the identity
 //   nu * omega * s * (n_out . grad xi_c) = +-G_bc / w_end     (normal axis b)
-// so the own normal flux is F_b / w_end at the face node and the lifting term
-// adds sigma * G_bc / w_end to F_c there; the neighbour's flux is rebuilt from
-// its normal node line (L2-resident) and its metric at the shared face.  The
-// three face axes are processed one after another so that no node is written
-// by two tasks at once: the result is deterministic without atomics.
+// with the contravariant fluxes F_b = sum_c G_bc d_c u (G_bc = w J nu grad xi_b . grad xi_c):
+// the own normal flux is F_b / w_end at the face node and the lifting term adds
+// sigma * G_bc / w_end to F_c there; the neighbour's flux is rebuilt from its normal node line
+// (L2-resident) and its metric at the shared face.  Every node's terms are summed by its owner in
+// a fixed order: the result is deterministic without atomics.
 // On unstructured meshes (ORIENT) the neighbour may meet a face with any of its faces and any
 // relative orientation (Sec. 5.1): its node line is then read at the orientation-mapped face
 // node, and its tangential derivatives are the own face grid's, exchanged and negated as the
@@ -20,32 +18,90 @@
 
 namespace dgfas {
 
+// elements per workgroup of the kernels with one thread per node
 template <int N>
 struct OpShape {
   static constexpr int N2 = N * N, N3 = N * N * N;
-  // LDS pitch of the xi_1 rows of volume tiles and of face rows: odd, so that the lanes of a
-  // wavefront that read one column of rows hit distinct banks
-  static constexpr int P = N | 1, V3 = N2 * P, F2 = N * P;
   static constexpr int EPB = (N3 >= 256) ? 1 : (256 / N3);
   static constexpr int THREADS = ((EPB * N3 + 63) / 64) * 64;
 };
 
-template <int N, typename T>
-struct OpSmem {
-  using S = OpShape<N>;
-  T sD[S::N2];                // D[i][m] at i N + m
-  T sDT[S::N2];               // D[i][m] at m N + i
-  T su[S::EPB][S::V3];
-  T sF[S::EPB][3][S::V3];
-  T sTr[S::EPB][6][S::F2];    // neighbour trace
-  T sRow[S::EPB][6][S::F2];   // direct face-row term
-  T sSig[S::EPB][6][S::F2];   // lifting weight sigma
-  double red[(S::THREADS + 63) / 64];   // per-wavefront partial sums of the fused dot product
+// The operator's tile: EPB elements, H threads per xi_3 column (i, j) of an element, each owning
+// KPT = ceil(N / H) of the column's nodes.  A node's metric, fluxes and lifting stay in its owner's
+// registers, a row of D is read once per thread and direction, and only u, the neighbours' traces,
+// the face terms and the fluxes on their way into the transposed contractions go through LDS.
+// One thread per node with everything in LDS needs about 105 LDS reads a node and, at p = 8, a
+// 768-thread workgroup of which one fits a CU; here a p = 8 element takes 243 threads and three
+// fit.  H and EPB were measured on 20^3 to 32^3 elements (one thread per node, chosen; best of the
+// other splits): p = 1: 9.1, 7.2; 7.5 us, p = 2: 26.1, 22.3; 23.2, p = 3: 55.6, 40.5; 41.4,
+// p = 4: 126.8, 111.5; 121.6, p = 5: 47.3, 37.9; 39.9, p = 6: 96.6, 70.1; 72.5,
+// p = 7: 418, 377; 387, p = 8: 215, 141; 236.
+template <int N>
+struct ColShape {
+  static constexpr int N2 = N * N, N3 = N * N * N;
+  static constexpr int HS[10] = {0, 0, 2, 3, 2, 3, 6, 4, 4, 3}, ES[10] = {0, 0, 8, 7, 4, 3, 1, 1, 1, 1};
+  static constexpr int H = HS[N], EPB = ES[N];
+  static constexpr int KPT = (N + H - 1) / H;
+  static constexpr int NR = (6 + H - 1) / H;                   // face tasks per thread
+  static constexpr int TE = N2 * H;                            // threads per element
+  static constexpr int THREADS = ((EPB * TE + 63) / 64) * 64;
+  static constexpr int P = N | 1, V3 = N2 * P, F2 = N * P;     // odd pitches: the lanes that read one
+                                                               // column of rows hit distinct banks
+  static constexpr bool FULL = EPB * TE == THREADS;
+  static constexpr bool UNIH = N2 == 64;                       // a wavefront is one slice of the columns
 };
 
-// One tile: EPB elements of one right-hand side (logical block lbr).  Every thread of the
-// workgroup passes every barrier; threads beyond EPB n^3 only take part in them, so the
-// tile also runs inside wider batched workgroups.
+template <typename T>
+struct alignas(2 * sizeof(T)) FacePair {
+  T a, s;   // a face node's row term without the own flux, and its lifting weight
+};
+
+template <int N, typename T>
+struct OpSmem {
+  using S = ColShape<N>;
+  T sD[S::N2];                         // D[i][m] at i N + m
+  T su[S::EPB][S::V3];                 // u, then the xi_1 fluxes
+  T sTr[S::EPB][6 * S::F2 > S::V3 ? 6 * S::F2 : S::V3];   // neighbour traces, then the xi_2 fluxes
+  T sF2[S::EPB][S::V3];                // xi_3 fluxes
+  FacePair<T> sAS[S::EPB][6][S::N2];
+  T sQ[S::EPB][6];                     // weight of the own flux in the row term: interior 1/2, Dirichlet 1
+  double red[4];                       // per-wavefront partial sums of the fused dot product
+};
+
+// nothing is moved across: keeps the loads of a later stage (and their registers) out of an
+// earlier one
+__device__ __forceinline__ void stage_fence() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+// x is computed here: keeps the compiler from moving a sum to its use, which holds every operand
+// in a register until then
+template <typename T>
+__device__ __forceinline__ void pin(T& x) {
+  asm volatile("" : "+v"(x));
+}
+// s + a0 b0 + a1 b1 + a2 b2 with the roundings spelled out, so that every form of the tile (its own
+// launch, one launch over several degrees, persistent) gives the same bits
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <typename T>
+__device__ __forceinline__ T add3(T s, T a0, T b0, T a1, T b1, T a2, T b2) {
+  return fma_(a2, b2, fma_(a1, b1, fma_(a0, b0, s)));
+}
+template <typename T>
+__device__ __forceinline__ T dot3(T a0, T b0, T a1, T b1, T a2, T b2) {
+  return fma_(a2, b2, fma_(a1, b1, a0 * b0));
+}
+// read-only data at a uniform address comes through the scalar cache also after a fence (the
+// constant address space has no aliases); vector loads of D and of the neighbour ids held the
+// p = 7 operator at 417 us (32^3), scalar ones brought it to 377
+template <typename T>
+using cptr = const __attribute__((address_space(4))) T*;
+template <typename T>
+__device__ __forceinline__ cptr<T> uniform_ptr(const T* p) {
+  return (cptr<T>)(uintptr_t)p;
+}
+
 // the neighbour's face node of own face node f under orientation code o (bit 0: exchange the
 // face axes, bits 1 and 2: reverse the first and the second)
 template <int N>
@@ -58,302 +114,368 @@ __device__ __forceinline__ int orient_face_node(int f, int o) {
 // first face axis of face phi (layout: phi 0/1 -> (xi_3, xi_2), 2/3 -> (xi_3, xi_1), 4/5 -> (xi_2, xi_1))
 __device__ __forceinline__ int face_axis_first(int phi) { return phi < 4 ? 2 : 1; }
 
-// tid_in: the thread index when the caller passes it (the persistent batches), else threadIdx.x
-// MORTAR: the level has faces between degrees (OpArgs::fmapE), whose terms the tile adds.
-template <int N, typename T, bool ORIENT = false, bool MORTAR = false>
-__device__ __forceinline__ void sipg_tile(const OpArgs<T>& a, const int lbr, OpSmem<N, T>& sm, int tid_in = -1) {
-  using S = OpShape<N>;
-  const int nrhs = a.nrhs, nel = a.nel, mode = a.mode;
-  const T* __restrict__ u = a.u;
-  const T* __restrict__ g = a.g;
-  T* __restrict__ out = a.out;
-  const T* __restrict__ G = a.G;
-  const T* __restrict__ WJ = a.WJ;
-  const T* __restrict__ pen = a.pen;
-  const int* __restrict__ nbr = a.nbr;
-  const int8_t* __restrict__ bc = a.bc;
-  const T* __restrict__ Dg = a.D;
-  const T kappa = a.kappa, inv_wend = a.inv_wend;
-  constexpr int N2 = S::N2, N3 = S::N3, EPB = S::EPB, P = S::P, V3 = S::V3, F2 = S::F2;
-  constexpr int TPT = (6 * N2 + N3 - 1) / N3;     // face tasks per thread
-  // logical block = (element block, right-hand side) with the right-hand side fastest, so
-  // that the batch of one element reads its geometry while it is resident in L2
-  const int lb = lbr / nrhs;
+// One tile: EPB elements of one right-hand side (logical block lbr = (element block, right-hand
+// side) with the right-hand side fastest, so that the batch of one element reads its geometry while
+// it is resident in L2).  Threads without an element load what another thread loads and write
+// nothing, so that no load sits behind a branch; the wavefronts of a wider batched workgroup
+// (WIDE) beyond THREADS only pass the barriers.
+// tid: the thread index (opaque in the persistent batches).
+// MIXED: a level of several degrees (per-element offsets; a neighbour of another degree is left
+// to the mortar face kernel, whose terms the tile adds through OpArgs::fmapE).
+template <int N, typename T, bool ORIENT, bool MIXED, bool WIDE>
+__device__ __forceinline__ void sipg_tile(const OpArgs<T>& a, const int lbr, OpSmem<N, T>& sm, const int tid) {
+  using S = ColShape<N>;
+  constexpr int N2 = S::N2, N3 = S::N3, H = S::H, KPT = S::KPT, NR = S::NR, TE = S::TE, EPB = S::EPB;
+  constexpr int P = S::P, F2 = S::F2;
+  constexpr bool CUT = N % H != 0;      // the last slice is short
+  constexpr bool ODD = 6 % H != 0;      // the last round of face tasks leaves slices idle
+  const bool live = !WIDE || tid < S::THREADS;
+  const int nrhs = a.nrhs, mode = a.mode;
+  const int lb = lbr / nrhs, rhs = lbr - lb * nrhs;
   const int64_t ndof = a.ndof;
-  const int64_t voff = (int64_t)(lbr - lb * nrhs) * ndof;
-  u += voff;
-  out += voff;
-  if (g) g += voff;
-  const int tid = tid_in >= 0 ? tid_in : (int)threadIdx.x;
-  const int le = tid / N3;
-  const int node = tid - le * N3;
-  const int li = lb * EPB + le;
-  const bool active = (le < EPB) && (li < nel);
-  const int e = active ? (a.elist ? a.elist[li] : li) : 0;
+  const T* __restrict__ u = a.u + (int64_t)rhs * ndof;
+  const T* __restrict__ g = a.g ? a.g + (int64_t)rhs * ndof : nullptr;
+  T* __restrict__ out = a.out + (int64_t)rhs * ndof;
+  const T* __restrict__ G = a.G;
+  const cptr<T> Dg = uniform_ptr(a.D);
+  const T inv_wend = a.inv_wend;
+  const int le0 = EPB == 1 ? 0 : tid / TE, t0 = tid - le0 * TE;
+  const bool act = S::FULL && !WIDE ? (EPB == 1 || lb * EPB + le0 < a.nel)
+                                    : (t0 < TE && le0 < EPB && lb * EPB + le0 < a.nel);
+  const int le = EPB == 1 || act ? le0 : 0, t = (S::FULL && !WIDE) || act ? t0 : 0;
+  int h = H == 1 ? 0 : t / N2;
+  const int col = t - h * N2;
+  if constexpr (S::UNIH) h = __builtin_amdgcn_readfirstlane(h);
+  const int i = col % N, j = col / N;
+  // the thread's q-th node along xi_3, and its r-th face; a thread beyond the last node or face
+  // repeats the last one
+  auto node = [&](int q) { return CUT ? min(h * KPT + q, N - 1) : h * KPT + q; };
+  auto face = [&](int r) { return ODD ? min(r * H + h, 5) : r * H + h; };
+  int e = lb * EPB + le;
+  if (a.elist) e = a.elist[e];
+  if constexpr (EPB == 1) e = __builtin_amdgcn_readfirstlane(e);
+  const int64_t base = MIXED ? a.off[e] : (int64_t)e * N3;
 
-  T(&sD)[N2] = sm.sD;
-  T(&sDT)[N2] = sm.sDT;
-  T(&su)[EPB][V3] = sm.su;
-  T(&sF)[EPB][3][V3] = sm.sF;
-  T(&sTr)[EPB][6][F2] = sm.sTr;
-  T(&sRow)[EPB][6][F2] = sm.sRow;
-  T(&sSig)[EPB][6][F2] = sm.sSig;
-  const int i = node % N, j = (node / N) % N, k = node / N2;
-  const int lnode = (k * N + j) * P + i;          // padded LDS slot of the thread's node
-
-  const int64_t base = a.off ? a.off[e] : (int64_t)e * N3;
-  const int64_t fbase = a.offF ? a.offF[e] : (int64_t)e * 6 * N2;
-  // prologue: every load that needs only the element goes out in one batch (the D table, u,
-  // the face tasks' neighbour ids, penalties and boundary codes, the metric, g) and nothing
-  // uses them before the batch is issued, so that the tile waits for memory once before the
-  // neighbour loads that need the neighbour ids
-  T dv = 0;
-  if (tid < N2) dv = Dg[tid];
-  int en_t[TPT];
-  T pen_t[TPT];
-  int8_t bc_t[TPT];
-  int fo_t[TPT];   // ORIENT: the neighbour's face | orientation << 3
+  T uv[KPT], pf[NR], gn[NR][3], dn[NR], trv[NR], G6[KPT][6], F[KPT][3], row[KPT], gv[KPT];
+  int en[NR], fo[NR];
+  int8_t bcv[NR];
+  if (live) {
+    for (int q = tid; q < N2; q += S::THREADS) sm.sD[q] = a.D[q];
+    const int64_t fbase = MIXED ? a.offF[e] : (int64_t)e * 6 * N2;
 #pragma unroll
-  for (int k = 0; k < TPT; ++k) {
-    en_t[k] = -1;
-    pen_t[k] = 0;
-    bc_t[k] = 0;
-    fo_t[k] = 0;
-  }
-  T uval = 0, gval = 0;
-  T gl[6] = {0, 0, 0, 0, 0, 0};
-  if (active) {
-    uval = u[base + node];
+    for (int q = 0; q < KPT; ++q) uv[q] = u[base + node(q) * N2 + col];
 #pragma unroll
-    for (int k = 0; k < TPT; ++k) {
-      const int t = node + k * N3;
-      if (t < 6 * N2) {
-        const int phi = t / N2;
-        en_t[k] = nbr[(int64_t)e * 6 + phi];
-        pen_t[k] = pen[fbase + t];
-        bc_t[k] = bc[(int64_t)e * 6 + phi];
-        if constexpr (ORIENT) fo_t[k] = a.nfo[(int64_t)e * 6 + phi];
+    for (int r = 0; r < NR; ++r) {
+      const int phi = face(r);
+      en[r] = S::UNIH && EPB == 1 ? uniform_ptr(a.nbr)[(int64_t)e * 6 + phi] : a.nbr[(int64_t)e * 6 + phi];
+      bcv[r] = a.bc[(int64_t)e * 6 + phi];
+      pf[r] = a.pen[fbase + phi * N2 + col];
+      fo[r] = ORIENT && en[r] >= 0 ? a.nfo[(int64_t)e * 6 + phi] : 0;
+      if (MIXED && en[r] >= 0 && a.deg[en[r]] != N - 1) en[r] = -2;
+    }
+    {
+      // the neighbour's node line along its normal and its metric row at the shared face; a face
+      // without one reads the element itself and uses nothing of it
+      T ln[NR][N];
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int phi = face(r);
+        const int phio = ORIENT ? (fo[r] & 7) : (phi ^ 1);
+        const int f = ORIENT ? orient_face_node<N>(col, fo[r] >> 3) : col;
+        const int axo = phio >> 1;
+        const int nb = en[r] >= 0 ? en[r] : e;
+        const int64_t nbase = MIXED ? a.off[nb] : (int64_t)nb * N3;
+        const T* __restrict__ line = u + nbase + face_node<N>(phio, f, 0);
+        const int st = axis_stride<N>(axo);
+#pragma unroll
+        for (int m = 0; m < N; ++m) ln[r][m] = line[m * st];
+        const int64_t gi = nbase + face_node<N>(phio, f, (phio & 1) ? N - 1 : 0);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) gn[r][c] = G[sym_index(axo, c) * ndof + gi];
       }
-    }
+      if (act) {
 #pragma unroll
-    for (int c = 0; c < 6; ++c) gl[c] = G[c * ndof + base + node];
-    if (mode == 0) gval = g[base + node];
-  }
-  if (tid < N2) {
-    sD[tid] = dv;
-    sDT[(tid % N) * N + tid / N] = dv;
-  }
-  if (active) su[le][lnode] = uval;
-  // phase 0: the neighbour data of every face node (normal node line and metric row) is
-  // loaded into registers here, as soon as the neighbour ids have arrived, and used from the
-  // neighbour trace on.  On levels of several degrees the neighbour's degree and offset go
-  // out together; a neighbour of another degree is left to the mortar face kernel (en = -2).
-  T lnv[TPT][N], gn[TPT][3];
-#pragma unroll
-  for (int k = 0; k < TPT; ++k) {
-    const int t = node + k * N3;
-#pragma unroll
-    for (int m = 0; m < N; ++m) lnv[k][m] = 0;
-    gn[k][0] = gn[k][1] = gn[k][2] = 0;
-    if (!active || t >= 6 * N2) continue;
-    const int phi = t / N2, f = t - phi * N2, ax = phi >> 1;
-    int en = en_t[k];
-    if (en < 0) continue;
-    const int64_t nbase = a.off ? a.off[en] : (int64_t)en * N3;
-    if (a.deg && a.deg[en] != N - 1) en = -2;
-    en_t[k] = en;
-    if (en >= 0) {
-      const int phio = ORIENT ? (fo_t[k] & 7) : (phi ^ 1);
-      const int fo = ORIENT ? orient_face_node<N>(f, fo_t[k] >> 3) : f;
-      const int axo = ORIENT ? (phio >> 1) : ax;
-      const int endo = (phio & 1) ? N - 1 : 0;
-      const T* line = u + nbase + face_node<N>(phio, fo, 0);
-      const int st = axis_stride<N>(axo);
-      const int64_t gi = nbase + face_node<N>(phio, fo, endo);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) gn[k][c] = G[sym_index(axo, c) * ndof + gi];
-#pragma unroll
-      for (int m = 0; m < N; ++m) lnv[k][m] = line[m * st];
-    }
-  }
-  __syncthreads();
-
-  // a wavefront is one xi_3 layer when N^2 = 64: D[k][m] and D[m][k] are then uniform and
-  // come through the scalar cache instead of LDS
-  constexpr bool kLayer = N * N == 64 && EPB == 1;
-  const int ku = kLayer ? __builtin_amdgcn_readfirstlane(k) : k;
-  // phase 1: reference derivatives and contravariant fluxes F_b = sum_c G_bc d_c u
-  if (active) {
-    T d0 = 0, d1 = 0, d2 = 0;
-#pragma unroll
-    for (int m = 0; m < N; ++m) {
-      d0 += sDT[m * N + i] * su[le][(k * N + j) * P + m];
-      d1 += sDT[m * N + j] * su[le][(k * N + m) * P + i];
-      d2 += (kLayer ? Dg[ku * N + m] : sDT[m * N + k]) * su[le][(m * N + j) * P + i];
-    }
-    sF[le][0][lnode] = gl[0] * d0 + gl[1] * d1 + gl[2] * d2;
-    sF[le][1][lnode] = gl[1] * d0 + gl[3] * d1 + gl[4] * d2;
-    sF[le][2][lnode] = gl[2] * d0 + gl[4] * d1 + gl[5] * d2;
-  }
-  // the neighbour's trace and normal derivative at every face node
-  T dn_nb[TPT];
-#pragma unroll
-  for (int k = 0; k < TPT; ++k) {
-    const int t = node + k * N3;
-    dn_nb[k] = 0;
-    if (!active || t >= 6 * N2) continue;
-    const int phi = t / N2, f = t - phi * N2;
-    T tr = 0;
-    if (en_t[k] >= 0) {
-      const int phio = ORIENT ? (fo_t[k] & 7) : (phi ^ 1);
-      const int endo = (phio & 1) ? N - 1 : 0;
-      T dn = 0;
-#pragma unroll
-      for (int m = 0; m < N; ++m) {
-        const T v = lnv[k][m];
-        dn += sD[endo * N + m] * v;
-        if (m == endo) tr = v;
+        for (int q = 0; q < KPT; ++q)
+          if (!CUT || h * KPT + q < N) sm.su[le][(node(q) * N + j) * P + i] = uv[q];
       }
-      dn_nb[k] = dn;
-    }
-    sTr[le][phi][(f / N) * P + f % N] = tr;
-  }
-  __syncthreads();
-
-  // phase 2: face terms per face node (no two tasks share an output slot)
 #pragma unroll
-  for (int kk = 0; kk < TPT; ++kk) {
-    const int t = node + kk * N3;
-    if (!active || t >= 6 * N2) continue;
-    const int phi = t / N2, f = t - phi * N2, ax = phi >> 1;
-    const int vi = face_node<N>(phi, f, (phi & 1) ? N - 1 : 0);
-    const int lvi = (vi / N) * P + vi % N;
-    const int fa = f / N, fb = f - fa * N, lf = fa * P + fb;
-    const T sgn = (phi & 1) ? T(1) : T(-1);
-    const T uo = su[le][lvi];
-    const T qo = sgn * inv_wend * sF[le][ax][lvi];   // nu omega s n_out . grad u
-    const T pf = pen_t[kk];
-    T row = 0, sigma = 0;
-    if (en_t[kk] >= 0) {
-      T dlast = 0, dfirst = 0;
+      for (int r = 0; r < NR; ++r) {
+        const int phi = face(r);
+        const int endo = ((ORIENT ? fo[r] : (phi ^ 1)) & 1) ? N - 1 : 0;
+        T s = 0, l0 = ln[r][0], l1 = ln[r][N - 1];
 #pragma unroll
-      for (int m = 0; m < N; ++m) {
-        dlast += sDT[m * N + fb] * sTr[le][phi][fa * P + m];
-        dfirst += sDT[m * N + fa] * sTr[le][phi][m * P + fb];
-      }
-      T du0, du1, du2;
-      T qn;
-      if constexpr (ORIENT) {
-        // the neighbour's reference derivatives: along its normal from its node line, along its
-        // face axes from the own face grid through the orientation
-        const int phio = fo_t[kk] & 7, o = fo_t[kk] >> 3;
-        const T dA = ((o & 2) ? T(-1) : T(1)) * ((o & 1) ? dlast : dfirst);
-        const T dB = ((o & 4) ? T(-1) : T(1)) * ((o & 1) ? dfirst : dlast);
-        const int an = phio >> 1, af = face_axis_first(phio);   // the third axis takes dB
-        du0 = an == 0 ? dn_nb[kk] : (af == 0 ? dA : dB);
-        du1 = an == 1 ? dn_nb[kk] : (af == 1 ? dA : dB);
-        du2 = an == 2 ? dn_nb[kk] : (af == 2 ? dA : dB);
-        const T fl = gn[kk][0] * du0 + gn[kk][1] * du1 + gn[kk][2] * du2;
-        qn = ((phio & 1) ? T(1) : T(-1)) * inv_wend * fl;   // neighbour's outward flux
-      } else {
-        if (ax == 0) { du0 = dn_nb[kk]; du1 = dlast; du2 = dfirst; }
-        else if (ax == 1) { du0 = dlast; du1 = dn_nb[kk]; du2 = dfirst; }
-        else { du0 = dlast; du1 = dfirst; du2 = dn_nb[kk]; }
-        const T fl = gn[kk][0] * du0 + gn[kk][1] * du1 + gn[kk][2] * du2;
-        qn = -sgn * inv_wend * fl;                   // neighbour's outward flux
-      }
-      const T jmp = uo - sTr[le][phi][lf];
-      row = pf * jmp - T(0.5) * (qo - qn);
-      sigma = T(-0.5) * jmp;
-    } else if (en_t[kk] == -1 && bc_t[kk] == 1) {    // Dirichlet: 2 mu nu omega s u - q, lifting -u
-      row = pf * uo - qo;
-      sigma = -uo;
-    }
-    sRow[le][phi][lf] = row;
-    sSig[le][phi][lf] = sigma;
-  }
-  __syncthreads();
-
-  // phase 3: every node collects the terms of the faces it lies on (its own slots)
-  T rowsum = 0;
-  if (active) {
-    const int fidx[3] = {k * P + j, k * P + i, j * P + i};
-    const int idx[3] = {i, j, k};
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-      int phi = -1;
-      if (idx[ax] == 0) phi = 2 * ax;
-      else if (idx[ax] == N - 1) phi = 2 * ax + 1;
-      if (phi < 0) continue;
-      rowsum += sRow[le][phi][fidx[ax]];
-      const T sg = sSig[le][phi][fidx[ax]] * ((phi & 1) ? inv_wend : -inv_wend);
-      sF[le][0][lnode] += sg * gl[sym_index(ax, 0)];
-      sF[le][1][lnode] += sg * gl[sym_index(ax, 1)];
-      sF[le][2][lnode] += sg * gl[sym_index(ax, 2)];
-      if constexpr (MORTAR) {
-        // a face to another degree: its row and lifting terms from the mortar face kernel
-        const int kf = a.fmapE[(int64_t)e * 6 + phi];
-        if (kf >= 0) {
-          const T* __restrict__ r = a.fres + (int64_t)(lbr - lb * nrhs) * a.fres_stride + (int64_t)kf * kMortarFaceRes;
-          const int ff = ax == 0 ? k * N + j : (ax == 1 ? k * N + i : j * N + i);
-          rowsum += r[ff];
-          sF[le][0][lnode] += r[81 + ff];
-          sF[le][1][lnode] += r[162 + ff];
-          sF[le][2][lnode] += r[243 + ff];
+        for (int m = 0; m < N; ++m) s = fma_(endo ? Dg[(N - 1) * N + m] : Dg[m], ln[r][m], s);
+        dn[r] = s;
+        if constexpr (ORIENT) {   // both ends stay in registers: a selected index would spill the line
+          pin(l0);
+          pin(l1);
         }
+        trv[r] = endo ? l1 : l0;
+        pin(dn[r]);
+        pin(trv[r]);
+        if (act && (!ODD || r * H + h < 6)) sm.sTr[le][phi * F2 + j * P + i] = trv[r];
+      }
+    }
+    stage_fence();
+    // the metric arrives while the derivatives are taken
+#pragma unroll
+    for (int q = 0; q < KPT; ++q)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) G6[q][c] = G[c * ndof + base + node(q) * N2 + col];
+  }
+  __syncthreads();
+
+  if (live) {
+    // reference derivatives of the own nodes and tangential derivatives of the neighbours'
+    // traces, one direction (and one row of D) after another
+    T dlast[NR], dfirst[NR];
+    {
+      T Dr[N];
+#pragma unroll
+      for (int m = 0; m < N; ++m) Dr[m] = sm.sD[i * N + m];
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) {
+        T s = 0;
+#pragma unroll
+        for (int m = 0; m < N; ++m) s = fma_(Dr[m], sm.su[le][(node(q) * N + j) * P + m], s);
+        F[q][0] = s;
+        pin(F[q][0]);
+        if (q & 1) stage_fence();
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        T s = 0;
+#pragma unroll
+        for (int m = 0; m < N; ++m) s = fma_(Dr[m], sm.sTr[le][face(r) * F2 + j * P + m], s);
+        dlast[r] = s;
+        pin(dlast[r]);
+        stage_fence();
+      }
+#pragma unroll
+      for (int m = 0; m < N; ++m) Dr[m] = sm.sD[j * N + m];
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) {
+        T s = 0;
+#pragma unroll
+        for (int m = 0; m < N; ++m) s = fma_(Dr[m], sm.su[le][(node(q) * N + m) * P + i], s);
+        F[q][1] = s;
+        pin(F[q][1]);
+        if (q & 1) stage_fence();
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        T s = 0;
+#pragma unroll
+        for (int m = 0; m < N; ++m) s = fma_(Dr[m], sm.sTr[le][face(r) * F2 + m * P + i], s);
+        dfirst[r] = s;
+        pin(dfirst[r]);
+        stage_fence();
+      }
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) F[q][2] = 0;
+#pragma unroll
+      for (int m = 0; m < N; ++m) {
+        const T um = sm.su[le][(m * N + j) * P + i];
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) F[q][2] = fma_(S::UNIH ? Dg[node(q) * N + m] : sm.sD[node(q) * N + m], um, F[q][2]);
+      }
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) pin(F[q][2]);
+    }
+    stage_fence();
+    // face terms that need no flux of the own element
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int phi = r * H + h, ax = phi >> 1;
+      if (ODD && phi > 5) continue;
+      const int vi = face_node<N>(phi, col, (phi & 1) ? N - 1 : 0);
+      const T uo = sm.su[le][(vi / N) * P + vi % N];
+      T A = 0, sig = 0, fq = 0;
+      if (en[r] >= 0) {
+        T du0, du1, du2, qn;   // the neighbour's reference derivatives and outward flux
+        if constexpr (ORIENT) {
+          // along its normal from its node line, along its face axes from the own face grid
+          // through the orientation
+          const int phio = fo[r] & 7, o = fo[r] >> 3;
+          const T dA = ((o & 2) ? T(-1) : T(1)) * ((o & 1) ? dlast[r] : dfirst[r]);
+          const T dB = ((o & 4) ? T(-1) : T(1)) * ((o & 1) ? dfirst[r] : dlast[r]);
+          const int an = phio >> 1, af = face_axis_first(phio);   // the third axis takes dB
+          du0 = an == 0 ? dn[r] : (af == 0 ? dA : dB);
+          du1 = an == 1 ? dn[r] : (af == 1 ? dA : dB);
+          du2 = an == 2 ? dn[r] : (af == 2 ? dA : dB);
+          qn = ((phio & 1) ? T(1) : T(-1)) * inv_wend * dot3(gn[r][0], du0, gn[r][1], du1, gn[r][2], du2);
+        } else {
+          if (ax == 0) { du0 = dn[r]; du1 = dlast[r]; du2 = dfirst[r]; }
+          else if (ax == 1) { du0 = dlast[r]; du1 = dn[r]; du2 = dfirst[r]; }
+          else { du0 = dlast[r]; du1 = dfirst[r]; du2 = dn[r]; }
+          qn = ((phi & 1) ? T(-1) : T(1)) * inv_wend * dot3(gn[r][0], du0, gn[r][1], du1, gn[r][2], du2);
+        }
+        const T jmp = uo - trv[r];
+        A = fma_(pf[r], jmp, T(0.5) * qn);
+        sig = T(-0.5) * jmp;
+        fq = T(0.5);
+      } else if (en[r] == -1 && bcv[r] == 1) {   // Dirichlet: 2 mu nu omega s u - q, lifting -u
+        A = pf[r] * uo;
+        sig = -uo;
+        fq = 1;
+      }
+      if (act) {
+        sm.sAS[le][phi][j * N + i] = FacePair<T>{A, sig};
+        if (col == 0) sm.sQ[le][phi] = fq;
+      }
+    }
+    stage_fence();
+    // contravariant fluxes F_b = sum_c G_bc d_c u
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+      const T d0 = F[q][0], d1 = F[q][1], d2 = F[q][2];
+      F[q][0] = dot3(G6[q][0], d0, G6[q][1], d1, G6[q][2], d2);
+      F[q][1] = dot3(G6[q][1], d0, G6[q][3], d1, G6[q][4], d2);
+      F[q][2] = dot3(G6[q][2], d0, G6[q][4], d1, G6[q][5], d2);
+      pin(F[q][0]);
+      pin(F[q][1]);
+      pin(F[q][2]);
+    }
+  }
+  __syncthreads();
+
+  if (live) {
+    // the owner of a face node adds its row term and lifts
+    const bool onx = i == 0 || i == N - 1, ony = j == 0 || j == N - 1;
+    const int px = i == 0 ? 0 : 1, py = j == 0 ? 2 : 3;
+    const T wx = i == 0 ? -inv_wend : inv_wend, wy = j == 0 ? -inv_wend : inv_wend;
+    T fx = 0, fy = 0;
+    if (onx) fx = sm.sQ[le][px] * wx;
+    if (ony) fy = sm.sQ[le][py] * wy;
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+      const int k = h * KPT + q;
+      row[q] = 0;
+      if (CUT && k >= N) continue;
+      T sx = 0, sy = 0, sz = 0;
+      if (onx) {
+        const FacePair<T> f = sm.sAS[le][px][k * N + j];
+        row[q] += fma_(-fx, F[q][0], f.a);
+        sx = f.s * wx;
+      }
+      if (ony) {
+        const FacePair<T> f = sm.sAS[le][py][k * N + i];
+        row[q] += fma_(-fy, F[q][1], f.a);
+        sy = f.s * wy;
+      }
+      if (k == 0 || k == N - 1) {
+        const int pz = k == 0 ? 4 : 5;
+        const T wz = k == 0 ? -inv_wend : inv_wend;
+        const FacePair<T> f = sm.sAS[le][pz][j * N + i];
+        row[q] += fma_(-(sm.sQ[le][pz] * wz), F[q][2], f.a);
+        sz = f.s * wz;
+      }
+      F[q][0] = add3(F[q][0], sx, G6[q][0], sy, G6[q][1], sz, G6[q][2]);
+      F[q][1] = add3(F[q][1], sx, G6[q][1], sy, G6[q][3], sz, G6[q][4]);
+      F[q][2] = add3(F[q][2], sx, G6[q][2], sy, G6[q][4], sz, G6[q][5]);
+      if constexpr (MIXED) {
+        // a face to another degree: its row and lifting terms from the mortar face kernel
+        if (a.fmapE) {
+          auto mortar = [&](int phi, int ff) {
+            const int kf = a.fmapE[(int64_t)e * 6 + phi];
+            if (kf < 0) return;
+            const T* __restrict__ m = a.fres + (int64_t)rhs * a.fres_stride + (int64_t)kf * kMortarFaceRes;
+            row[q] += m[ff];
+            F[q][0] += m[81 + ff];
+            F[q][1] += m[162 + ff];
+            F[q][2] += m[243 + ff];
+          };
+          if (onx) mortar(px, k * N + j);
+          if (ony) mortar(py, k * N + i);
+          if (k == 0 || k == N - 1) mortar(k == 0 ? 4 : 5, j * N + i);
+        }
+      }
+      if (act) {
+        const int l = (k * N + j) * P + i;
+        sm.su[le][l] = F[q][0];
+        sm.sTr[le][l] = F[q][1];
+        sm.sF2[le][l] = F[q][2];
       }
     }
   }
   __syncthreads();
 
   double pq = 0;
-  if (active) {
-    T acc = rowsum;
+  if (live) {
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) gv[q] = mode == 0 ? g[base + node(q) * N2 + col] : T(0);
+    T Dr[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) Dr[m] = sm.sD[m * N + i];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+#pragma unroll
+      for (int m = 0; m < N; ++m) row[q] = fma_(Dr[m], sm.su[le][(node(q) * N + j) * P + m], row[q]);
+      pin(row[q]);
+      if (q & 1) stage_fence();
+    }
+    stage_fence();
+#pragma unroll
+    for (int m = 0; m < N; ++m) Dr[m] = sm.sD[m * N + j];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+#pragma unroll
+      for (int m = 0; m < N; ++m) row[q] = fma_(Dr[m], sm.sTr[le][(node(q) * N + m) * P + i], row[q]);
+      pin(row[q]);
+      if (q & 1) stage_fence();
+    }
+    stage_fence();
 #pragma unroll
     for (int m = 0; m < N; ++m) {
-      acc += sD[m * N + i] * sF[le][0][(k * N + j) * P + m];
-      acc += sD[m * N + j] * sF[le][1][(k * N + m) * P + i];
-      acc += (kLayer ? Dg[m * N + ku] : sD[m * N + k]) * sF[le][2][(m * N + j) * P + i];
+      const T fm = sm.sF2[le][(m * N + j) * P + i];
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) row[q] = fma_(S::UNIH ? Dg[m * N + node(q)] : sm.sD[m * N + node(q)], fm, row[q]);
     }
-    if (WJ) acc += kappa * WJ[base + node] * uval;
-    out[base + node] = mode == 0 ? gval - acc : acc;
-    if (a.dotp) pq = (double)uval * (double)acc;
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+      if (!act || (CUT && h * KPT + q >= N)) continue;
+      const int64_t o = base + node(q) * N2 + col;
+      T acc = row[q];
+      if (a.WJ) acc = fma_(a.kappa * a.WJ[o], uv[q], acc);
+      out[o] = mode == 0 ? gv[q] - acc : acc;
+      pq += (double)uv[q] * (double)acc;
+    }
   }
-  if (a.dotp) {
+  if (!MIXED && a.dotp) {
     // u^T (A u) over the tile: wavefront butterfly, then the waves in order (deterministic)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) pq += __shfl_xor(pq, off);
-    if ((tid & 63) == 0 && tid < S::THREADS) sm.red[tid >> 6] = pq;
+    if ((tid & 63) == 0) sm.red[tid >> 6] = pq;
     __syncthreads();
     if (tid == 0) {
       double s = 0;
-      for (int w = 0; w < (S::THREADS + 63) / 64; ++w) s += sm.red[w];
-      const int nlb = (nel + EPB - 1) / EPB;
-      a.dotp[(int64_t)(lbr - lb * nrhs) * nlb + lb] = s;
+      for (int w = 0; w < S::THREADS / 64; ++w) s += sm.red[w];
+      a.dotp[(int64_t)rhs * ((a.nel + EPB - 1) / EPB) + lb] = s;
     }
   }
 }
 
-template <int N, typename T, bool ORIENT, bool MORTAR>
-__global__ void __launch_bounds__(OpShape<N>::THREADS)
+template <int N, typename T, bool ORIENT, bool MIXED>
+__global__ void __launch_bounds__(ColShape<N>::THREADS)
 sipg_apply_kernel(OpArgs<T> a) {
-  using S = OpShape<N>;
+  using S = ColShape<N>;
   __shared__ OpSmem<N, T> sm;
   const int lbr = xcd_block(((a.nel + S::EPB - 1) / S::EPB) * a.nrhs);
   if (lbr < 0) return;
-  sipg_tile<N, T, ORIENT, MORTAR>(a, lbr, sm);
+  sipg_tile<N, T, ORIENT, MIXED, false>(a, lbr, sm, threadIdx.x);
 }
 
 template <int N, typename T>
 void launch_sipg(const OpArgs<T>& a, hipStream_t st) {
-  using S = OpShape<N>;
+  using S = ColShape<N>;
   const int nb = ((a.nel + S::EPB - 1) / S::EPB) * a.nrhs;
-  if (a.nfo) hipLaunchKernelGGL((sipg_apply_kernel<N, T, true, false>), dim3(xcd_grid(nb)), dim3(S::THREADS), 0, st, a);
-  else if (a.fmapE) hipLaunchKernelGGL((sipg_apply_kernel<N, T, false, true>), dim3(xcd_grid(nb)), dim3(S::THREADS), 0, st, a);
-  else hipLaunchKernelGGL((sipg_apply_kernel<N, T, false, false>), dim3(xcd_grid(nb)), dim3(S::THREADS), 0, st, a);
+  const dim3 gr(xcd_grid(nb)), bl(S::THREADS);
+  if (a.nfo) hipLaunchKernelGGL((sipg_apply_kernel<N, T, true, false>), gr, bl, 0, st, a);
+  else if (a.off) hipLaunchKernelGGL((sipg_apply_kernel<N, T, false, true>), gr, bl, 0, st, a);
+  else hipLaunchKernelGGL((sipg_apply_kernel<N, T, false, false>), gr, bl, 0, st, a);
 }
 
-// largest tile workspace of the degrees with n <= N
+// largest tile workspace and widest tile of the degrees with n <= N
 template <typename T, int N>
 constexpr size_t op_smem_upto() {
   if constexpr (N < 2) {
@@ -363,10 +485,19 @@ constexpr size_t op_smem_upto() {
     return a > b ? a : b;
   }
 }
+template <int N>
+constexpr int op_threads_upto() {
+  if constexpr (N < 2) {
+    return 0;
+  } else {
+    constexpr int a = ColShape<N>::THREADS, b = op_threads_upto<N - 1>();
+    return a > b ? a : b;
+  }
+}
 
 // all degrees up to NMAX - 1 in one launch; the workgroup is the widest tile's
 template <int NMAX, typename T, bool PERSIST>
-__global__ void __launch_bounds__(OpShape<NMAX>::THREADS)
+__global__ void __launch_bounds__(op_threads_upto<NMAX>())
 sipg_batched_kernel(OpArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, int ntiles) {
   __shared__ __align__(16) char smem[op_smem_upto<T, NMAX>()];
   // tiles dealt round-robin over the XCDs (the hardware order): the work list runs from the
@@ -376,11 +507,8 @@ sipg_batched_kernel(OpArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, i
   // through an opaque register copy in every tile, so that no degree branch's index arithmetic
   // is hoisted above the loop and kept live across it (that cost 48 VGPRs and scratch).
   auto tile = [&](int t) {
-    int tid = -1;
-    if constexpr (PERSIST) {
-      tid = threadIdx.x;
-      asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"(tid));
-    }
+    int tid = threadIdx.x;
+    if constexpr (PERSIST) asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"(tid));
     const int k = find_bucket(bd, nb, kStageOp, t);
     OpArgs<T> x = a;
     x.nel = bd[k].nel;
@@ -391,7 +519,7 @@ sipg_batched_kernel(OpArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, i
     switch (bd[k].p) {
 #define DGFAS_OPB(P)                                                                        \
   case P:                                                                                   \
-    if constexpr (P + 1 <= NMAX) sipg_tile<P + 1, T, false, true>(x, lbr, *reinterpret_cast<OpSmem<P + 1, T>*>(smem), tid); \
+    if constexpr (P + 1 <= NMAX) sipg_tile<P + 1, T, false, true, true>(x, lbr, *reinterpret_cast<OpSmem<P + 1, T>*>(smem), tid); \
     break;
       DGFAS_OPB(1) DGFAS_OPB(2) DGFAS_OPB(3) DGFAS_OPB(4) DGFAS_OPB(5) DGFAS_OPB(6) DGFAS_OPB(7) DGFAS_OPB(8)
 #undef DGFAS_OPB
@@ -409,18 +537,20 @@ sipg_batched_kernel(OpArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, i
 }
 
 int stage_tiles(int stage, int p, int nel, int nrhs) {
-  const int n3 = (p + 1) * (p + 1) * (p + 1);
-  const int epb = n3 >= 256 ? 1 : 256 / n3;   // elements per tile of the operator and overlap add
   if (stage == kStageSolve) return nel * nrhs;
+  const int n3 = (p + 1) * (p + 1) * (p + 1);
+  const int epb = stage == kStageOp ? ColShape<2>::ES[p + 1] : (n3 >= 256 ? 1 : 256 / n3);   // elements per tile
   return ((nel + epb - 1) / epb) * nrhs;
 }
 
 int stage_threads(int stage, int pmax) {
   const int n = pmax + 1, n3 = n * n * n;
   if (stage == kStageSolve) return n + 2 >= 9 ? 128 : 64;   // overlap 1: ns^2 lines, rounded to waves
+  if (stage == kStageOp) return 256;   // op_threads_upto of every NMAX that is launched
   if (n3 >= 256) return ((n3 + 63) / 64) * 64;
   return 256;
 }
+static_assert(op_threads_upto<6>() == 256 && op_threads_upto<9>() == 256, "workgroup of the batched operator");
 
 template <typename T>
 void sipg_apply_batched(int pmax, const OpArgs<T>& a, const BucketDesc<T>* bd, const BatchLaunch& l, hipStream_t st) {
