@@ -12,6 +12,8 @@
 // per-element overlap buffer.
 // schwarz_overlap_add: gather form of the scatter, z[node] += contributions of
 // the neighbours' subdomains in a fixed order -- deterministic, no atomics.
+#include <type_traits>
+
 #include "device.hpp"
 #include "kernels.hpp"
 
@@ -43,234 +45,216 @@ int overlap_size(int p, int m) {
 
 template <int N, int M, typename T>
 struct SzSmem {
-  using Sh = SzShape<N, M>;
-  T tA[Sh::TILE];             // the subdomain tile; every contraction updates its own lines in place
-  T sW[3][Sh::NS];
-  int sMap[3][Sh::NS];
-  int sNb[27];
+  T tA[SzShape<N, M>::TILE];   // the subdomain tile; every contraction updates its own lines in place
   int sOff[27];
 };
 
+// side variant v = left * 4 + right; only an interior side, code 0, has overlap
+template <int M>
+__device__ __forceinline__ int lo_layers(int v) {
+  return (v >> 2) == 0 ? M : 0;
+}
+template <int M>
+__device__ __forceinline__ int hi_layers(int v) {
+  return (v & 3) == 0 ? M : 0;
+}
+// node of subdomain position q along a direction of variant v: (delta + 1) * 64 + local index, or
+// -1 for padding.  The same as the host's table SchwarzArgs::map1d, without a load that waits
+// for the variant.
+template <int N, int M>
+__device__ __forceinline__ int tile_map(int v, int q) {
+  const int d = q - lo_layers<M>(v);
+  if (d < 0) return N - M + q;
+  if (d < N) return 64 + d;
+  return d - N < hi_layers<M>(v) ? 128 + d - N : -1;
+}
+
+// read-only table at a uniform address, through the scalar cache
+template <typename T>
+using ctab = const __attribute__((address_space(4))) T*;
+template <typename T>
+__device__ __forceinline__ ctab<T> table(const T* p) {
+  return (ctab<T>)(uintptr_t)p;
+}
+
+// out_c = sum_q Mt[c][q] in_q for a tile line in registers
+template <int NS, typename T>
+__device__ __forceinline__ T line_row(ctab<T> Mt, int c, const T (&in)[NS]) {
+  T s = 0;
+#pragma unroll
+  for (int q = 0; q < NS; ++q) s += Mt[c * NS + q] * in[q];
+  return s;
+}
+
 // One subdomain solve (logical block lbr = element in the list, right-hand side fastest).
 // Threads at or beyond THR (wider batched workgroups) only pass the barriers.
+//
+// The contractions run xi_3, xi_2, xi_1, divide, xi_1, xi_2, xi_3 with one thread per tile line: the
+// first takes the gathered column from registers, the two around the division stay in registers
+// and the last one's results go straight to their destinations, so the tile passes through LDS
+// four times (8 accesses a point) and the workgroup meets at four barriers.  With the xi_3 pair in
+// the middle, and the gather, the scatter and every contraction through LDS (14 accesses, seven
+// barriers, node maps and weights staged behind one more), the 32^3, p = 7 solve took
+// 204 us in FP64 (157 in FP32), now 174 (126); m = 3, 20^3, p = 8: 185, now 156.
+// A column's destinations in z or an inbox are one pointer and a stride.
+// The eigenvector rows are uniform over the workgroup and come through the scalar cache into SGPR
+// operands.
 template <int N, int M, typename T>
 __device__ __forceinline__ void schwarz_tile(SchwarzArgs<T> a, const int lbr, SzSmem<N, M, T>& sm, int tid_in = -1) {
   using Sh = SzShape<N, M>;
-  constexpr int NS = Sh::NS, LS = Sh::LS, THR = Sh::THREADS;
+  constexpr int NS = Sh::NS, LS = Sh::LS;
   constexpr Regions<N, M> R{};
   const int li = lbr / a.nrhs, rhs = lbr - li * a.nrhs;   // right-hand side fastest
-  const int e = a.elist ? a.elist[li] : li;
+  const int e = __builtin_amdgcn_readfirstlane(a.elist ? a.elist[li] : li);
   if (a.sel && !a.sel[e]) return;
   a.r += (int64_t)rhs * a.ndof;
   a.z += (int64_t)rhs * a.ndof;
   a.O += (int64_t)rhs * a.nin;
   const int tid = tid_in >= 0 ? tid_in : (int)threadIdx.x;   // tid_in: from a persistent batch
-
   T(&tA)[Sh::TILE] = sm.tA;
-  T(&sW)[3][NS] = sm.sW;
-  int(&sMap)[3][NS] = sm.sMap;
-  int(&sNb)[27] = sm.sNb;
   int(&sOff)[27] = sm.sOff;
+  if (M > 0 && tid < 27) sOff[tid] = R.off[tid];
 
-  // variant per direction: uniform over the workgroup, so the eigenvector tables
-  // are read through the scalar cache straight into SGPR operands
+  // variant per direction: uniform over the workgroup
   const int v0 = __builtin_amdgcn_readfirstlane(a.var[(int64_t)e * 3 + 0]);
   const int v1 = __builtin_amdgcn_readfirstlane(a.var[(int64_t)e * 3 + 1]);
   const int v2 = __builtin_amdgcn_readfirstlane(a.var[(int64_t)e * 3 + 2]);
-  const T* __restrict__ S1 = a.S + v0 * NS * NS;
-  const T* __restrict__ S2 = a.S + v1 * NS * NS;
-  const T* __restrict__ S3 = a.S + v2 * NS * NS;
-  const T* __restrict__ L3 = a.lam + v2 * NS;
-  for (int t = tid; t < 3 * NS; t += THR) {
-    const int d = t / NS, q = t - d * NS;
-    const int v = d == 0 ? v0 : (d == 1 ? v1 : v2);
-    sW[d][q] = a.W[v * NS + q];
-    sMap[d][q] = a.map1d[v * NS + q];
-  }
-  if (tid < 27) {
-    int nb = a.nb27[(int64_t)e * 27 + tid];
-    if (nb >= 0 && a.deg && a.deg[nb] != N - 1) nb = -1;   // another degree: zero fill, no scatter
-    sNb[tid] = nb;
-    sOff[tid] = R.off[tid];
-  }
-  const T g0 = a.gco[(int64_t)e * 4 + 0], g1 = a.gco[(int64_t)e * 4 + 1];
-  const T g2 = a.gco[(int64_t)e * 4 + 2], g3 = a.gco[(int64_t)e * 4 + 3];
-  __syncthreads();
+  const ctab<T> S1 = table(a.S) + v0 * NS * NS, S1T = table(a.ST) + v0 * NS * NS;
+  const ctab<T> S2 = table(a.S) + v1 * NS * NS, S2T = table(a.ST) + v1 * NS * NS;
+  const ctab<T> S3 = table(a.S) + v2 * NS * NS, S3T = table(a.ST) + v2 * NS * NS;
 
   // gather r_s = R_s r, one thread per xi_3 column (s1, s2) of the tile: the column's
   // node (l1, l2) in each of the three elements it crosses is found once, the xi_3
-  // positions (uniform over the workgroup) then only select the element and the layer.
-  // Every load of a thread is issued before its LDS stores.
+  // positions (uniform over the workgroup) then only select the element and the layer
   const bool act = tid < NS * NS;
   const int c1 = tid % NS, c2 = tid / NS;
-  int m3u[NS];
+  const int m1 = tile_map<N, M>(v0, c1), m2 = act ? tile_map<N, M>(v1, c2) : -1;
+  const bool in = m1 >= 0 && m2 >= 0;
+  int nb[3] = {-1, -1, -1};   // the elements the column crosses; absent ones: zeros, no scatter
+  if (in) {
 #pragma unroll
-  for (int s3 = 0; s3 < NS; ++s3) m3u[s3] = __builtin_amdgcn_readfirstlane(sMap[2][s3]);
-  if (act) {
-    const int m1 = sMap[0][c1], m2 = sMap[1][c2];
-    int64_t cb[3];
+    for (int d3 = 0; d3 < 3; ++d3) nb[d3] = a.nb27[(int64_t)e * 27 + d3 * 9 + (m2 >> 6) * 3 + (m1 >> 6)];
+    if (a.deg) {
 #pragma unroll
-    for (int d3 = 0; d3 < 3; ++d3) {
-      cb[d3] = -1;
-      if (m1 >= 0 && m2 >= 0) {
-        const int src = sNb[d3 * 9 + (m2 >> 6) * 3 + (m1 >> 6)];   // absent neighbour: zeros
-        if (src >= 0) cb[d3] = elem_base<N>(a, src) + (m2 & 63) * N + (m1 & 63);
-      }
+      for (int d3 = 0; d3 < 3; ++d3)
+        if (nb[d3] >= 0 && a.deg[nb[d3]] != N - 1) nb[d3] = -1;   // another degree: zero fill, no scatter
     }
-    T vals[NS];
-#pragma unroll
-    for (int s3 = 0; s3 < NS; ++s3) {
-      const int m3 = m3u[s3];
-      vals[s3] = 0;
-      if (m3 >= 0) {
-        const int64_t cbase = cb[m3 >> 6];
-        if (cbase >= 0) vals[s3] = a.r[cbase + (m3 & 63) * (N * N)];
-      }
-    }
-#pragma unroll
-    for (int s3 = 0; s3 < NS; ++s3) tA[(s3 * NS + c2) * LS + c1] = vals[s3];
   }
-  __syncthreads();
-
-  // Each contraction: one thread per tile line, out_c = sum_q M[c][q] line_q with the
-  // row M[c][:] read through the scalar cache (uniform over the workgroup).
-  const int tlo = c1, thi = c2;
-  const T* __restrict__ S1T = a.ST + v0 * NS * NS;
-  const T* __restrict__ S2T = a.ST + v1 * NS * NS;
-  const T* __restrict__ S3T = a.ST + v2 * NS * NS;
+  const int l12 = (m2 & 63) * N + (m1 & 63);
+  const bool lo3 = M > 0 && lo_layers<M>(v2) != 0, hi3 = M > 0 && hi_layers<M>(v2) != 0;
   T line[NS];
-  // phase 1: xi_1 with S1^T   (thread: s2 = tlo, s3 = thi)
+#pragma unroll
+  for (int q = 0; q < NS; ++q) line[q] = 0;
+  // the column's layers below, in and above the element; LO = M or 0, the layers below in use
+  auto gather = [&](auto lo) {
+    constexpr int LO = decltype(lo)::value;
+    if (nb[1] >= 0) {
+      const T* __restrict__ p = a.r + elem_base<N>(a, nb[1]) + l12;
+#pragma unroll
+      for (int l = 0; l < N; ++l) line[LO + l] = p[l * N * N];
+    }
+    if (LO > 0 && nb[0] >= 0) {
+      const T* __restrict__ p = a.r + elem_base<N>(a, nb[0]) + l12;
+#pragma unroll
+      for (int l = 0; l < LO; ++l) line[l] = p[(N - M + l) * N * N];
+    }
+    if (hi3 && nb[2] >= 0) {
+      const T* __restrict__ p = a.r + elem_base<N>(a, nb[2]) + l12;
+#pragma unroll
+      for (int l = 0; l < M; ++l) line[LO + N + l] = p[l * N * N];
+    }
+  };
+  if (lo3) gather(std::integral_constant<int, M>{});
+  else gather(std::integral_constant<int, 0>{});
+  // xi_3 with S3^T   (thread: s1 = c1, s2 = c2)
   if (act) {
-    const int b = (thi * NS + tlo) * LS;
+#pragma unroll
+    for (int c = 0; c < NS; ++c) tA[(c * NS + c2) * LS + c1] = line_row<NS, T>(S3T, c, line);
+  }
+  __syncthreads();
+  // xi_2 with S2^T   (thread: s1 = c1, s3 = c2)
+  if (act) {
+#pragma unroll
+    for (int q = 0; q < NS; ++q) line[q] = tA[(c2 * NS + q) * LS + c1];
+#pragma unroll
+    for (int c = 0; c < NS; ++c) tA[(c2 * NS + c) * LS + c1] = line_row<NS, T>(S2T, c, line);
+  }
+  __syncthreads();
+  // xi_1 with S1^T, divide by D, xi_1 with S1   (thread: s2 = c1, s3 = c2)
+  if (act) {
+    const int b = (c2 * NS + c1) * LS;
 #pragma unroll
     for (int q = 0; q < NS; ++q) line[q] = tA[b + q];
-#pragma unroll 1
-    for (int c = 0; c < NS; ++c) {
-      T s = 0;
+    const T g0 = a.gco[(int64_t)e * 4 + 0], g1 = a.gco[(int64_t)e * 4 + 1];
+    const T g2 = a.gco[(int64_t)e * 4 + 2], g3 = a.gco[(int64_t)e * 4 + 3];
+    const ctab<T> lam1 = table(a.lam) + v0 * NS;
+    const T base = g0 + g2 * a.lam[v1 * NS + c1] + g3 * a.lam[v2 * NS + c2];
+    T w[NS];
 #pragma unroll
-      for (int q = 0; q < NS; ++q) s += S1T[c * NS + q] * line[q];
-      tA[b + c] = s;
-    }
+    for (int c = 0; c < NS; ++c) w[c] = line_row<NS, T>(S1T, c, line) / (base + g1 * lam1[c]);
+#pragma unroll
+    for (int c = 0; c < NS; ++c) tA[b + c] = line_row<NS, T>(S1, c, w);
   }
   __syncthreads();
-  // phase 2: xi_2 with S2^T   (thread: s1 = tlo, s3 = thi)
+  // xi_2 with S2   (thread: s1 = c1, s3 = c2)
   if (act) {
 #pragma unroll
-    for (int q = 0; q < NS; ++q) line[q] = tA[(thi * NS + q) * LS + tlo];
-#pragma unroll 1
-    for (int c = 0; c < NS; ++c) {
-      T s = 0;
+    for (int q = 0; q < NS; ++q) line[q] = tA[(c2 * NS + q) * LS + c1];
 #pragma unroll
-      for (int q = 0; q < NS; ++q) s += S2T[c * NS + q] * line[q];
-      tA[(thi * NS + c) * LS + tlo] = s;
-    }
+    for (int c = 0; c < NS; ++c) tA[(c2 * NS + c) * LS + c1] = line_row<NS, T>(S2, c, line);
   }
   __syncthreads();
-  // phase 3: xi_3 with S3^T, divide by D, xi_3 with S3   (thread: s1 = tlo, s2 = thi);
-  // the thread's own k-line of tA holds the intermediate
-  if (act) {
+  // xi_3 with S3 and the weighted scatter   (thread: s1 = c1, s2 = c2): own part to z, each overlap
+  // part into the receiving element's inbox (region seen from the receiver), read back by
+  // overlap_add.  The destination of the column in each of the three xi_3 elements is found once;
+  // the xi_3 positions select it.
+  if (in) {
 #pragma unroll
-    for (int q = 0; q < NS; ++q) line[q] = tA[(q * NS + thi) * LS + tlo];
-    const T base = g0 + g1 * a.lam[v0 * NS + tlo] + g2 * a.lam[v1 * NS + thi];
-#pragma unroll 1
-    for (int c = 0; c < NS; ++c) {
-      T s = 0;
+    for (int q = 0; q < NS; ++q) line[q] = tA[(q * NS + c2) * LS + c1];
+    const int d1 = (m1 >> 6) - 1, d2 = (m2 >> 6) - 1, l1 = m1 & 63, l2 = m2 & 63;
+    const bool own = d1 == 0 && d2 == 0;
+    const T w12 = a.W[v0 * NS + c1] * a.W[v1 * NS + c2];
+    const ctab<T> W3 = table(a.W) + v2 * NS;
+    // weighted value of position s3, whose node is l12 + l N^2 of element en
+    auto value = [&](int s3, int en, int l) -> T {
+      T t = line_row<NS, T>(S3, s3, line);
+      if (a.corr) t += (T)(a.cscale[e] * (double)a.corr[(int64_t)e * (NS * NS * NS) + (s3 * NS + c2) * NS + c1]);
+      T v = a.unweighted ? t : w12 * W3[s3] * t;
+      if (a.cinv && !a.unweighted) v *= a.cinv[elem_base<N>(a, en) + l12 + l * (N * N)];   // normalised weight
+      return v;
+    };
+    // first inbox slot of the column in the element at xi_3 offset d3, and the slots per layer
+    const int x1 = d1 ? M : N, x2 = d2 ? M : N;
+    const int cc = (d2 < 0 ? l2 - (N - M) : l2) * x1 + (d1 < 0 ? l1 - (N - M) : l1);
+    const int ds = own ? N * N : x2 * x1;
+    auto inbox = [&](int d3) -> T* {
+      const int r = (1 - d3) * 9 + (1 - d2) * 3 + (1 - d1);      // direction from the receiver back to e
+      return a.O + inbox_base<N, M>(a, nb[d3 + 1]) + sOff[r] + cc;
+    };
+    auto scatter = [&](auto lo) {
+      constexpr int LO = decltype(lo)::value;
+      if (nb[1] >= 0) {
+        T* __restrict__ p = own ? a.z + elem_base<N>(a, e) + l12 : inbox(0);
 #pragma unroll
-      for (int q = 0; q < NS; ++q) s += S3T[c * NS + q] * line[q];
-      tA[(c * NS + thi) * LS + tlo] = s / (base + g3 * L3[c]);
-    }
-#pragma unroll
-    for (int q = 0; q < NS; ++q) line[q] = tA[(q * NS + thi) * LS + tlo];
-#pragma unroll 1
-    for (int c = 0; c < NS; ++c) {
-      T s = 0;
-#pragma unroll
-      for (int q = 0; q < NS; ++q) s += S3[c * NS + q] * line[q];
-      tA[(c * NS + thi) * LS + tlo] = s;
-    }
-  }
-  __syncthreads();
-  // phase 4: xi_2 with S2   (thread: s1 = tlo, s3 = thi)
-  if (act) {
-#pragma unroll
-    for (int q = 0; q < NS; ++q) line[q] = tA[(thi * NS + q) * LS + tlo];
-#pragma unroll 1
-    for (int c = 0; c < NS; ++c) {
-      T s = 0;
-#pragma unroll
-      for (int q = 0; q < NS; ++q) s += S2[c * NS + q] * line[q];
-      tA[(thi * NS + c) * LS + tlo] = s;
-    }
-  }
-  __syncthreads();
-  // phase 5: xi_1 with S1   (thread: s2 = tlo, s3 = thi)
-  if (act) {
-    const int b = (thi * NS + tlo) * LS;
-#pragma unroll
-    for (int q = 0; q < NS; ++q) line[q] = tA[b + q];
-#pragma unroll 1
-    for (int c = 0; c < NS; ++c) {
-      T s = 0;
-#pragma unroll
-      for (int q = 0; q < NS; ++q) s += S1[c * NS + q] * line[q];
-      tA[b + c] = s;
-    }
-  }
-  __syncthreads();
-  // weighted scatter, one thread per xi_3 column (s1, s2): own part to z, each overlap part
-  // into the receiving element's inbox (region seen from the receiver), read back by
-  // overlap_add.  The destination of the column in each of the three xi_3 elements is
-  // found once; the xi_3 positions select it.
-  if (act) {
-    const int m1 = sMap[0][c1], m2 = sMap[1][c2];
-    if (m1 >= 0 && m2 >= 0) {
-      const int d1 = (m1 >> 6) - 1, d2 = (m2 >> 6) - 1, l1 = m1 & 63, l2 = m2 & 63;
-      const T w12 = sW[0][c1] * sW[1][c2];
-      int64_t db[3], nbase[3];   // nbase: the column's node (l1, l2, 0) in the receiving element
-      int ds[3];
-#pragma unroll
-      for (int d3i = 0; d3i < 3; ++d3i) {
-        const int d3 = d3i - 1;
-        db[d3i] = -1;
-        ds[d3i] = 0;
-        nbase[d3i] = 0;
-        if (d1 == 0 && d2 == 0 && d3 == 0) {
-          db[d3i] = elem_base<N>(a, e) + l2 * N + l1;
-          ds[d3i] = N * N;
-          nbase[d3i] = db[d3i];
-        } else {
-          const int dest = sNb[d3i * 9 + (d2 + 1) * 3 + (d1 + 1)];
-          if (dest >= 0) {
-            nbase[d3i] = elem_base<N>(a, dest) + l2 * N + l1;
-            const int r = (1 - d3) * 9 + (1 - d2) * 3 + (1 - d1);      // direction from dest back to e
-            const int cc1 = d1 < 0 ? l1 - (N - M) : l1, cc2 = d2 < 0 ? l2 - (N - M) : l2;
-            const int x1 = d1 ? M : N, x2 = d2 ? M : N;
-            ds[d3i] = x2 * x1;
-            db[d3i] = inbox_base<N, M>(a, dest) + sOff[r] + cc2 * x1 + cc1;
-          }
+        for (int l = 0; l < N; ++l) {
+          T v = value(LO + l, nb[1], l);
+          if (own && a.mode != 0) v += p[l * N * N];
+          p[l * ds] = v;
         }
       }
+      if (LO > 0 && nb[0] >= 0) {
+        T* __restrict__ p = inbox(-1);
 #pragma unroll
-      for (int s3 = 0; s3 < NS; ++s3) {
-        const int m3 = m3u[s3];
-        if (m3 < 0) continue;
-        const int d3i = m3 >> 6, l3 = m3 & 63;
-        T t = tA[(s3 * NS + c2) * LS + c1];
-        if (a.corr) t += (T)(a.cscale[e] * (double)a.corr[(int64_t)e * (NS * NS * NS) + (s3 * NS + c2) * NS + c1]);
-        T v = a.unweighted ? t : w12 * sW[2][s3] * t;
-        const int64_t base = db[d3i];
-        if (base < 0) continue;
-        if (a.cinv && !a.unweighted) v *= a.cinv[nbase[d3i] + l3 * (N * N)];   // normalised weight
-        const int c3 = d3i == 0 ? l3 - (N - M) : l3;   // layer index inside the receiver's region
-        const int64_t gi = base + (int64_t)c3 * ds[d3i];
-        if (d1 == 0 && d2 == 0 && d3i == 1) {
-          if (a.mode == 0) a.z[gi] = v;
-          else a.z[gi] += v;
-        } else {
-          a.O[gi] = v;
-        }
+        for (int l = 0; l < LO; ++l) p[l * x2 * x1] = value(l, nb[0], N - M + l);
       }
-    }
+      if (hi3 && nb[2] >= 0) {
+        T* __restrict__ p = inbox(1);
+#pragma unroll
+        for (int l = 0; l < M; ++l) p[l * x2 * x1] = value(LO + N + l, nb[2], l);
+      }
+    };
+    if (lo3) scatter(std::integral_constant<int, M>{});
+    else scatter(std::integral_constant<int, 0>{});
   }
 }
 
@@ -418,7 +402,9 @@ struct AddShape {
 };
 
 template <int N, int M, typename T>
-__global__ void __launch_bounds__((SzShape<N, M>::THREADS))
+// eight waves per SIMD (64 registers, where the larger tiles have room in LDS): the two-wave
+// workgroups hide each other's gather and barriers (32^3, p = 7: 180 us at six waves, 174 at eight)
+__global__ void __launch_bounds__((SzShape<N, M>::THREADS), 8)
 schwarz_solve_kernel(SchwarzArgs<T> a) {
   __shared__ SzSmem<N, M, T> sm;
   const int lbr = xcd_block(a.nel * a.nrhs);
@@ -426,29 +412,54 @@ schwarz_solve_kernel(SchwarzArgs<T> a) {
   schwarz_tile<N, M, T>(a, lbr, sm);
 }
 
+template <int N, int M, typename T>
 struct AddSmem {
+  static constexpr int OSZ = Regions<N, M>{}.size;
+  T box[AddShape<N>::EPB][OSZ];   // the elements' inboxes
   int sOff[27];
   double red[2][16];   // per-wavefront partial sums of the fused dot products
 };
 
-// z[node] += sum of the neighbours' overlap contributions in the element's own
-// inbox, in a fixed order.  Inbox regions of absent neighbours stay zero.  With dotz set,
-// also the tile's sums of z dr and z (dr - dr0) over every node (deterministic order).
+// Sum of the neighbours' overlap contributions to node (l0, l1, l2) from the element's staged
+// inbox, in a fixed order (the up to 7 regions whose overlap covers the node).  Inbox regions of
+// absent neighbours stay zero.
 template <int N, int M, typename T>
-__device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr, AddSmem& sm, int tid_in = -1) {
+__device__ __forceinline__ T inbox_sum(const T* box, const int* sOff, const int (&l)[3], const int (&od)[3]) {
+  T acc = 0;
+#pragma unroll
+  for (int bits = 1; bits < 8; ++bits) {
+    const bool valid = ((bits & 1) == 0 || od[0] != 0) && ((bits & 2) == 0 || od[1] != 0) &&
+                       ((bits & 4) == 0 || od[2] != 0);
+    if (!valid) continue;
+    const int dd[3] = {(bits & 1) ? od[0] : 0, (bits & 2) ? od[1] : 0, (bits & 4) ? od[2] : 0};
+    const int r = (dd[2] + 1) * 9 + (dd[1] + 1) * 3 + (dd[0] + 1);
+    const int c1 = dd[0] > 0 ? l[0] - (N - M) : l[0];
+    const int c2 = dd[1] > 0 ? l[1] - (N - M) : l[1];
+    const int c3 = dd[2] > 0 ? l[2] - (N - M) : l[2];
+    const int x1 = dd[0] ? M : N, x2 = dd[1] ? M : N;
+    acc += box[sOff[r] + (c3 * x2 + c2) * x1 + c1];
+  }
+  return acc;
+}
+
+// z[node] += sum of the neighbours' overlap contributions in the element's own inbox.  The inbox
+// is one contiguous block and comes into LDS with coalesced loads: reading the up to 7 entries of
+// every node from global memory kept the address units busy 79 % of the launch (32^3, p = 7:
+// 128 us with seven loads a node, now 104).  With dotz set, also the tile's sums of z dr and z (dr - dr0)
+// over every node (deterministic order).
+template <int N, int M, typename T>
+__device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr, AddSmem<N, M, T>& sm, int tid_in = -1) {
   using Sh = AddShape<N>;
-  constexpr int N3 = Sh::N3, EPB = Sh::EPB;
+  constexpr int N3 = Sh::N3, EPB = Sh::EPB, OSZ = AddSmem<N, M, T>::OSZ;
   constexpr Regions<N, M> R{};
   const int lb = lbr / a.nrhs, rhs = lbr - lb * a.nrhs;
   a.z += (int64_t)rhs * a.ndof;
   a.O += (int64_t)rhs * a.nin;
   const int tid = tid_in >= 0 ? tid_in : (int)threadIdx.x;
-  int(&sOff)[27] = sm.sOff;
-  if (tid < 27) sOff[tid] = R.off[tid];
+  if (tid < 27) sm.sOff[tid] = R.off[tid];
   const int le = tid / N3, node = tid - le * N3;
   const int li = lb * EPB + le;
   const bool act = le < EPB && li < a.nel;
-  // the loads that need no region table go out ahead of the barrier
   int64_t gi = 0;
   int e = 0, l[3] = {0, 0, 0}, od[3] = {0, 0, 0};
   bool any = false;
@@ -456,6 +467,11 @@ __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr
   double rv = 0, r0v = 0;
   if (act) {
     e = a.elist ? a.elist[li] : li;
+    const T* __restrict__ box = a.O + inbox_base<N, M>(a, e);
+    constexpr int NB = (OSZ + N3 - 1) / N3;
+    T in[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) in[k] = box[min(node + k * N3, OSZ - 1)];
     gi = elem_base<N>(a, e) + node;
     l[0] = node % N;
     l[1] = (node / N) % N;
@@ -472,38 +488,16 @@ __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr
       rv = (double)a.dr[ri];
       if (a.dr0) r0v = (double)a.dr0[ri];
     }
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+      if (node + k * N3 < OSZ) sm.box[le][node + k * N3] = in[k];
   }
   __syncthreads();
   double pz = 0, pz2 = 0;
   if (act) {
     T zv = z0;
     if (any) {
-      const T* __restrict__ box = a.O + inbox_base<N, M>(a, e);
-      // the up to 7 candidates (subsets of the non-zero directions): every load is issued
-      // unconditionally (invalid ones read entry 0 and are masked) so that none waits on another
-      T vals[7];
-      bool ok[7];
-#pragma unroll
-      for (int bits = 1; bits < 8; ++bits) {
-        const int dd[3] = {(bits & 1) ? od[0] : 0, (bits & 2) ? od[1] : 0, (bits & 4) ? od[2] : 0};
-        const bool valid = ((bits & 1) == 0 || od[0] != 0) && ((bits & 2) == 0 || od[1] != 0) &&
-                           ((bits & 4) == 0 || od[2] != 0);
-        int off = 0;
-        if (valid) {
-          const int r = (dd[2] + 1) * 9 + (dd[1] + 1) * 3 + (dd[0] + 1);
-          const int c1 = dd[0] > 0 ? l[0] - (N - M) : l[0];
-          const int c2 = dd[1] > 0 ? l[1] - (N - M) : l[1];
-          const int c3 = dd[2] > 0 ? l[2] - (N - M) : l[2];
-          const int x1 = dd[0] ? M : N, x2 = dd[1] ? M : N;
-          off = sOff[r] + (c3 * x2 + c2) * x1 + c1;
-        }
-        ok[bits - 1] = valid;
-        vals[bits - 1] = box[off];
-      }
-      T acc = 0;
-#pragma unroll
-      for (int t = 0; t < 7; ++t) acc += ok[t] ? vals[t] : T(0);
-      zv = z0 + acc;
+      zv = z0 + inbox_sum<N, M, T>(sm.box[le], sm.sOff, l, od);
       a.z[gi] = zv;
     }
     if (a.dotz) {
@@ -539,7 +533,7 @@ template <int N, int M, typename T>
 __global__ void __launch_bounds__(AddShape<N>::THREADS)
 schwarz_overlap_add_kernel(SchwarzArgs<T> a) {
   using Sh = AddShape<N>;
-  __shared__ AddSmem sm;
+  __shared__ AddSmem<N, M, T> sm;
   const int lbr = xcd_block(((a.nel + Sh::EPB - 1) / Sh::EPB) * a.nrhs);
   if (lbr < 0) return;
   overlap_add_tile<N, M, T>(a, lbr, sm);
@@ -714,9 +708,11 @@ void launch_schwarz(const SchwarzArgs<T>& a, hipStream_t st) {
 
 template <int N, int M, typename T>
 void launch_overlap(const SchwarzArgs<T>& a, hipStream_t st) {
-  using Sh = AddShape<N>;
-  const int nb = ((a.nel + Sh::EPB - 1) / Sh::EPB) * a.nrhs;
-  hipLaunchKernelGGL((schwarz_overlap_add_kernel<N, M, T>), dim3(xcd_grid(nb)), dim3(Sh::THREADS), 0, st, a);
+  if constexpr (M > 0) {
+    using Sh = AddShape<N>;
+    const int nb = ((a.nel + Sh::EPB - 1) / Sh::EPB) * a.nrhs;
+    hipLaunchKernelGGL((schwarz_overlap_add_kernel<N, M, T>), dim3(xcd_grid(nb)), dim3(Sh::THREADS), 0, st, a);
+  }
 }
 
 #define DGFAS_SZ_CASES(F)                                                       \
@@ -810,10 +806,20 @@ schwarz_batched_kernel(SchwarzArgs<T> a, const BucketDesc<T>* __restrict__ bd, i
   }
 }
 
+template <typename T, int N>
+constexpr size_t add_smem_upto() {
+  if constexpr (N < 2) {
+    return 0;
+  } else {
+    constexpr size_t a = sizeof(AddSmem<N, 1, T>), b = add_smem_upto<T, N - 1>();
+    return a > b ? a : b;
+  }
+}
+
 template <int NMAX, typename T, bool PERSIST>
 __global__ void __launch_bounds__(AddShape<NMAX>::THREADS)
 overlap_add_batched_kernel(SchwarzArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, int ntiles) {
-  __shared__ AddSmem sm;
+  __shared__ __align__(16) char smem[add_smem_upto<T, NMAX>()];
   // tiles dealt round-robin over the XCDs (the hardware order), strided in the persistent form
   auto tile = [&](int t) {
     int tid = -1;   // persistent form: an opaque copy per tile (see sipg_batched_kernel)
@@ -829,7 +835,7 @@ overlap_add_batched_kernel(SchwarzArgs<T> a, const BucketDesc<T>* __restrict__ b
     switch (bd[k].p) {
 #define DGFAS_ADB(P)                                                          \
   case P:                                                                     \
-    if constexpr (P + 1 <= NMAX) overlap_add_tile<P + 1, 1, T>(x, lbr, sm, tid);  \
+    if constexpr (P + 1 <= NMAX) overlap_add_tile<P + 1, 1, T>(x, lbr, *reinterpret_cast<AddSmem<P + 1, 1, T>*>(smem), tid); \
     break;
       DGFAS_ADB(1) DGFAS_ADB(2) DGFAS_ADB(3) DGFAS_ADB(4) DGFAS_ADB(5) DGFAS_ADB(6) DGFAS_ADB(7) DGFAS_ADB(8)
 #undef DGFAS_ADB
