@@ -25,6 +25,31 @@ __device__ __forceinline__ int find_bucket(const D* __restrict__ bd, int nb, int
   return k;
 }
 
+// Sum over the wavefront, in every lane: lanes 1, 2, 4 and 8 apart within a row of 16, then the
+// rows, with DPP moves (a shuffle of doubles goes through LDS twice per step).  The order is fixed.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_add<0x111>(v);   // row_shr:1, absent lanes read zero
+  v = dpp_add<0x112>(v);   // row_shr:2
+  v = dpp_add<0x114>(v);   // row_shr:4
+  v = dpp_add<0x118>(v);   // row_shr:8: lane 15 of every row has the row's sum
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  double s = 0;
+#pragma unroll
+  for (int row = 0; row < 4; ++row) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, 16 * row + 15);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 16 * row + 15);
+    s += __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+  }
+  return s;
+}
+
 // Volume index of face node f = (a, b) of face phi (layout: phi 0/1 -> (k, j),
 // 2/3 -> (k, i), 4/5 -> (j, i)) with the normal index set to `t`.
 template <int N>

@@ -3,6 +3,8 @@
 // used for P (projection), R = I^T (restriction) and I (prolongation).
 // K4: BLAS-1 pieces of SCG (Alg. 6) with fixed-shape two-stage reductions, so
 // every dot product is bitwise reproducible.
+#include <algorithm>
+
 #include "device.hpp"
 #include "kernels.hpp"
 #include "blas.hpp"
@@ -265,15 +267,16 @@ void project_mean(int64_t n, int nrhs, double* v, double* partial, hipStream_t s
   hipLaunchKernelGGL(subtract_mean_kernel, dim3(nb, nrhs), dim3(kRedThreads), 0, st, n, nb, v, partial);
 }
 
+// sum over the workgroup in thread 0 (the wavefronts' sums in order); sh: one slot per wavefront
 __device__ __forceinline__ double block_sum(double v, double* sh) {
   const int tid = threadIdx.x;
-  sh[tid] = v;
+  v = wave_sum(v);
+  if ((tid & 63) == 0) sh[tid >> 6] = v;
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (tid < s) sh[tid] += sh[tid + s];
-    __syncthreads();
-  }
-  return sh[0];
+  double s = 0;
+  if (tid == 0)
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += sh[w];
+  return s;
 }
 
 // Batched reductions: vectors are [nrhs][n]; block (blk, rhs) writes
@@ -283,7 +286,7 @@ template <typename T>
 __global__ void __launch_bounds__(kRedThreads)
 dot_partial_kernel(int64_t n, const T* __restrict__ a, const T* __restrict__ b, const T* __restrict__ c,
                    double* __restrict__ partial) {
-  __shared__ double sh[kRedThreads];
+  __shared__ double sh[kRedThreads / 64];
   const int64_t off = (int64_t)blockIdx.y * n;
   a += off;
   if (b) b += off;
@@ -318,16 +321,31 @@ __global__ void __launch_bounds__(1024) finish_kernel(int nblocks, const double*
                                                       const double* __restrict__ partial2, int op,
                                                       double* __restrict__ scal, double* __restrict__ out,
                                                       int pstride) {
-  __shared__ double sh[1024];
-  const int tid = threadIdx.x, rhs = blockIdx.x;
+  __shared__ double sh[2][16];
+  const int tid = threadIdx.x, rhs = blockIdx.x, nt = blockDim.x;
+  const double* __restrict__ p1 = partial + (int64_t)rhs * pstride;
+  const double* __restrict__ p2 = partial2 + (int64_t)rhs * pstride;   // read for kOpBeta only
+  const bool two = op == kOpBeta;
   double v0 = 0, v1 = 0;
-  for (int b = tid; b < nblocks; b += 1024) {
-    v0 += partial[(int64_t)rhs * pstride + b];
-    if (op == kOpBeta) v1 += partial2[(int64_t)rhs * pstride + b];
+  // eight partials per step, all loads ahead of the sums: one load at a time waited for memory
+  // 32 times over the 32768 tiles of a 32^3, p = 7 level (17 us a launch; now 8)
+  for (int b0 = tid; b0 < nblocks; b0 += 8 * nt) {
+    double x[8], y[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int b = min(b0 + k * nt, nblocks - 1);
+      x[k] = p1[b];
+      y[k] = two ? p2[b] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (b0 + k * nt < nblocks) {
+        v0 += x[k];
+        v1 += y[k];
+      }
   }
-  const double s0 = block_sum(v0, sh);
-  __syncthreads();
-  const double s1 = (op == kOpBeta) ? block_sum(v1, sh) : 0.0;
+  const double s0 = block_sum(v0, sh[0]);
+  const double s1 = two ? block_sum(v1, sh[1]) : 0.0;
   if (tid != 0) return;
   double* sc = scal + rhs * 8;
   switch (op) {
@@ -365,8 +383,9 @@ __global__ void __launch_bounds__(1024) finish_kernel(int nblocks, const double*
 
 void finish(int nblocks, int nrhs, const double* partial, const double* partial2, int op, double* scal, double* out,
             hipStream_t st, int pstride) {
-  hipLaunchKernelGGL(finish_kernel, dim3(nrhs), dim3(1024), 0, st, nblocks, partial, partial2, op, scal, out,
-                     pstride);
+  // as many wavefronts as the partial sums fill with eight each, at most sixteen
+  const int thr = std::min(1024, std::max(64, (nblocks / 8 + 63) / 64 * 64));
+  hipLaunchKernelGGL(finish_kernel, dim3(nrhs), dim3(thr), 0, st, nblocks, partial, partial2, op, scal, out, pstride);
 }
 
 // p = beta p + z   (first: p = z), per right-hand side beta
@@ -414,7 +433,7 @@ template <typename T>
 __global__ void __launch_bounds__(kRedThreads)
 cg_update_kernel(int64_t n, const T* __restrict__ rin, T* __restrict__ rout, const T* __restrict__ q,
                  const double* __restrict__ scal, double* __restrict__ partial) {
-  __shared__ double sh[kRedThreads];
+  __shared__ double sh[kRedThreads / 64];
   const int rhs = blockIdx.y;
   const int64_t off = (int64_t)rhs * n;
   rin += off; rout += off; q += off;

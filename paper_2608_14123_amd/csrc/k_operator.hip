@@ -442,9 +442,8 @@ __device__ __forceinline__ void sipg_tile(const OpArgs<T>& a, const int lbr, OpS
     }
   }
   if (!MIXED && a.dotp) {
-    // u^T (A u) over the tile: wavefront butterfly, then the waves in order (deterministic)
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) pq += __shfl_xor(pq, off);
+    // u^T (A u) over the tile: the wavefronts' sums in order (deterministic)
+    pq = wave_sum(pq);
     if ((tid & 63) == 0) sm.red[tid >> 6] = pq;
     __syncthreads();
     if (tid == 0) {
@@ -538,17 +537,13 @@ sipg_batched_kernel(OpArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, i
 
 int stage_tiles(int stage, int p, int nel, int nrhs) {
   if (stage == kStageSolve) return nel * nrhs;
-  const int n3 = (p + 1) * (p + 1) * (p + 1);
-  const int epb = stage == kStageOp ? ColShape<2>::ES[p + 1] : (n3 >= 256 ? 1 : 256 / n3);   // elements per tile
+  const int epb = stage == kStageOp ? ColShape<2>::ES[p + 1] : kAddElems[p + 1];   // elements per tile
   return ((nel + epb - 1) / epb) * nrhs;
 }
 
 int stage_threads(int stage, int pmax) {
-  const int n = pmax + 1, n3 = n * n * n;
-  if (stage == kStageSolve) return n + 2 >= 9 ? 128 : 64;   // overlap 1: ns^2 lines, rounded to waves
-  if (stage == kStageOp) return 256;   // op_threads_upto of every NMAX that is launched
-  if (n3 >= 256) return ((n3 + 63) / 64) * 64;
-  return 256;
+  if (stage == kStageSolve) return pmax + 3 >= 9 ? 128 : 64;   // overlap 1: ns^2 lines, rounded to waves
+  return 256;   // the operator's widest tile (of every NMAX that is launched) and the overlap add's
 }
 static_assert(op_threads_upto<6>() == 256 && op_threads_upto<9>() == 256, "workgroup of the batched operator");
 

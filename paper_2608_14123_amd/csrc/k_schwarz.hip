@@ -396,9 +396,8 @@ schwarz_point_kernel(SchwarzArgs<T> a) {
 
 template <int N>
 struct AddShape {
-  static constexpr int N3 = N * N * N;
-  static constexpr int EPB = (N3 >= 256) ? 1 : (256 / N3);
-  static constexpr int THREADS = ((EPB * N3 + 63) / 64) * 64;
+  static constexpr int N3 = N * N * N, EPB = kAddElems[N], THREADS = 256;
+  static constexpr int KN = (EPB * N3 + THREADS - 1) / THREADS;   // nodes per thread
 };
 
 template <int N, int M, typename T>
@@ -417,7 +416,7 @@ struct AddSmem {
   static constexpr int OSZ = Regions<N, M>{}.size;
   T box[AddShape<N>::EPB][OSZ];   // the elements' inboxes
   int sOff[27];
-  double red[2][16];   // per-wavefront partial sums of the fused dot products
+  double red[2][AddShape<N>::THREADS / 64];   // per-wavefront partial sums of the fused dot products
 };
 
 // Sum of the neighbours' overlap contributions to node (l0, l1, l2) from the element's staged
@@ -445,80 +444,78 @@ __device__ __forceinline__ T inbox_sum(const T* box, const int* sOff, const int 
 // z[node] += sum of the neighbours' overlap contributions in the element's own inbox.  The inbox
 // is one contiguous block and comes into LDS with coalesced loads: reading the up to 7 entries of
 // every node from global memory kept the address units busy 79 % of the launch (32^3, p = 7:
-// 128 us with seven loads a node, now 104).  With dotz set, also the tile's sums of z dr and z (dr - dr0)
-// over every node (deterministic order).
+// 128 us with seven loads a node, 104 from LDS with one node a thread, now 73; with the dot
+// products 154, now 123, in FP32 122, now 71).  With dotz set, also the tile's sums of z dr and
+// z (dr - dr0) over every node (deterministic order).
 template <int N, int M, typename T>
 __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr, AddSmem<N, M, T>& sm, int tid_in = -1) {
   using Sh = AddShape<N>;
-  constexpr int N3 = Sh::N3, EPB = Sh::EPB, OSZ = AddSmem<N, M, T>::OSZ;
+  constexpr int N3 = Sh::N3, EPB = Sh::EPB, KN = Sh::KN, THR = Sh::THREADS, OSZ = AddSmem<N, M, T>::OSZ;
+  constexpr int NB = (EPB * OSZ + THR - 1) / THR;
   constexpr Regions<N, M> R{};
   const int lb = lbr / a.nrhs, rhs = lbr - lb * a.nrhs;
   a.z += (int64_t)rhs * a.ndof;
   a.O += (int64_t)rhs * a.nin;
   const int tid = tid_in >= 0 ? tid_in : (int)threadIdx.x;
   if (tid < 27) sm.sOff[tid] = R.off[tid];
-  const int le = tid / N3, node = tid - le * N3;
-  const int li = lb * EPB + le;
-  const bool act = le < EPB && li < a.nel;
-  int64_t gi = 0;
-  int e = 0, l[3] = {0, 0, 0}, od[3] = {0, 0, 0};
-  bool any = false;
-  T z0 = 0;
-  double rv = 0, r0v = 0;
-  if (act) {
-    e = a.elist ? a.elist[li] : li;
-    const T* __restrict__ box = a.O + inbox_base<N, M>(a, e);
-    constexpr int NB = (OSZ + N3 - 1) / N3;
-    T in[NB];
+  const int ne = min(EPB, a.nel - lb * EPB);   // elements of this tile
+  auto element = [&](int le) {
+    const int li = lb * EPB + min(le, ne - 1);
+    return a.elist ? a.elist[li] : li;
+  };
+  T in[NB], z0[KN];
 #pragma unroll
-    for (int k = 0; k < NB; ++k) in[k] = box[min(node + k * N3, OSZ - 1)];
-    gi = elem_base<N>(a, e) + node;
-    l[0] = node % N;
-    l[1] = (node / N) % N;
-    l[2] = node / (N * N);
-    // per direction the offset towards the one neighbour whose overlap can cover this node
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      od[d] = (l[d] < M) ? -1 : ((l[d] >= N - M) ? 1 : 0);
-      any = any || od[d] != 0;
-    }
-    if (any || a.dotz) z0 = a.z[gi];
-    if (a.dotz) {
-      const int64_t ri = (int64_t)rhs * a.ndof + gi;
-      rv = (double)a.dr[ri];
-      if (a.dr0) r0v = (double)a.dr0[ri];
-    }
-#pragma unroll
-    for (int k = 0; k < NB; ++k)
-      if (node + k * N3 < OSZ) sm.box[le][node + k * N3] = in[k];
+  for (int k = 0; k < NB; ++k) {
+    const int t = min(tid + k * THR, EPB * OSZ - 1), le = t / OSZ;
+    in[k] = a.O[inbox_base<N, M>(a, element(le)) + (t - le * OSZ)];
   }
+  int64_t gi[KN];
+  double rv[KN], r0v[KN];
+#pragma unroll
+  for (int k = 0; k < KN; ++k) {
+    const int t = min(tid + k * THR, EPB * N3 - 1), le = t / N3;
+    gi[k] = elem_base<N>(a, element(le)) + (t - le * N3);
+    z0[k] = a.z[gi[k]];
+    rv[k] = r0v[k] = 0;
+    if (a.dotz) {
+      const int64_t ri = (int64_t)rhs * a.ndof + gi[k];
+      rv[k] = (double)a.dr[ri];
+      if (a.dr0) r0v[k] = (double)a.dr0[ri];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NB; ++k)
+    if (tid + k * THR < EPB * OSZ) sm.box[(tid + k * THR) / OSZ][(tid + k * THR) % OSZ] = in[k];
   __syncthreads();
   double pz = 0, pz2 = 0;
-  if (act) {
-    T zv = z0;
-    if (any) {
-      zv = z0 + inbox_sum<N, M, T>(sm.box[le], sm.sOff, l, od);
-      a.z[gi] = zv;
+#pragma unroll
+  for (int k = 0; k < KN; ++k) {
+    const int t = tid + k * THR, le = t / N3, node = t - le * N3;
+    if (le >= ne) continue;
+    const int l[3] = {node % N, (node / N) % N, node / (N * N)};
+    // per direction the offset towards the one neighbour whose overlap can cover this node
+    int od[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) od[d] = (l[d] < M) ? -1 : ((l[d] >= N - M) ? 1 : 0);
+    T zv = z0[k];
+    if (od[0] != 0 || od[1] != 0 || od[2] != 0) {
+      zv += inbox_sum<N, M, T>(sm.box[le], sm.sOff, l, od);
+      a.z[gi[k]] = zv;
     }
-    if (a.dotz) {
-      pz = (double)zv * rv;
-      if (a.dr0) pz2 = (double)zv * (rv - r0v);
-    }
+    pz += (double)zv * rv[k];
+    if (a.dr0) pz2 += (double)zv * (rv[k] - r0v[k]);
   }
   if (a.dotz) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      pz += __shfl_xor(pz, off);
-      pz2 += __shfl_xor(pz2, off);
-    }
-    if ((tid & 63) == 0 && tid < Sh::THREADS) {
+    pz = wave_sum(pz);
+    pz2 = wave_sum(pz2);
+    if ((tid & 63) == 0) {
       sm.red[0][tid >> 6] = pz;
       sm.red[1][tid >> 6] = pz2;
     }
     __syncthreads();
     if (tid == 0) {
       double s = 0, s2 = 0;
-      for (int w = 0; w < Sh::THREADS / 64; ++w) {
+      for (int w = 0; w < THR / 64; ++w) {
         s += sm.red[0][w];
         s2 += sm.red[1][w];
       }
