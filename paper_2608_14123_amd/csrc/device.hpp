@@ -34,19 +34,25 @@ __device__ __forceinline__ double dpp_add(double v) {
   const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
   return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-__device__ __forceinline__ double wave_sum(double v) {
+// the value of one lane, uniform
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// sums of the rows of 16 lanes, in each row's last lane
+__device__ __forceinline__ double row_sum(double v) {
   v = dpp_add<0x111>(v);   // row_shr:1, absent lanes read zero
   v = dpp_add<0x112>(v);   // row_shr:2
   v = dpp_add<0x114>(v);   // row_shr:4
-  v = dpp_add<0x118>(v);   // row_shr:8: lane 15 of every row has the row's sum
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  return dpp_add<0x118>(v);   // row_shr:8
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = row_sum(v);
   double s = 0;
 #pragma unroll
-  for (int row = 0; row < 4; ++row) {
-    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, 16 * row + 15);
-    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 16 * row + 15);
-    s += __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-  }
+  for (int row = 0; row < 4; ++row) s += lane_value(v, 16 * row + 15);
   return s;
 }
 

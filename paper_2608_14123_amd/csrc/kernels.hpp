@@ -274,6 +274,27 @@ void rows_sumsq(const int* list, int n, int n3, const double* v, double* out, hi
 template <typename T>
 bool htransfer(int p, const HXferArgs<T>& a, hipStream_t st);
 
+// One-launch root solve (k_root.hip): a p = 1 level of one degree with at most kSmallRootElems elements,
+// overlap 1, structured neighbours
+constexpr int kSmallRootElems = 64;
+struct SmallRootArgs {
+  int E = 0, n = 0;                 // elements; iteration cap
+  int check = 1;                    // a breakdown ends the solve at a multiple of this many iterations
+  double rtol = 0;                  // stop at |r| <= rtol |r_0|; 0: exactly n iterations
+  int project = 0;                  // 1: residuals are projected to zero mean
+  double kappa = 0, inv_wend = 0;
+  double* u = nullptr;              // [nrhs][8 E]
+  const double* g = nullptr;
+  const double *G = nullptr, *WJ = nullptr, *pen = nullptr, *D = nullptr;
+  const int* nbr = nullptr;
+  const int8_t* bc = nullptr;
+  const int* nb27 = nullptr;
+  const int8_t* var = nullptr;
+  const double *gco = nullptr, *S = nullptr, *lam = nullptr, *W = nullptr;
+  double* scal = nullptr;           // [nrhs][8]: 4 breakdown, 5 iterations, 7 converged
+};
+void small_root(const SmallRootArgs& a, int nrhs, hipStream_t st);
+
 int reduction_blocks(int64_t n);
 
 }  // namespace dgfas

@@ -752,7 +752,42 @@ struct Solver {
   // FD contractions of the FP32 smoother on matrix cores (BF16 or FP32 operands)
   bool matrix_cores() const { return opt.precision == DGFAS_BF16 || opt.precision == DGFAS_FP32_MFMA; }
 
-  int root_solve(double* u, const double* g, bool* breakdown) {
+  // The one-launch root solve covers a structured p = 1 root of at most 64 elements with overlap 1:
+  // its workgroup has sixteen threads per element, and above that the general kernels fill more
+  // than one CU.  4^3, p = 1: 8 launches of 2 to 5 us an iteration there, 8 us an iteration here.
+  bool small_root_fits() const {
+    const Level& L = lv[0];
+    return L.uniform && !L.lr && !L.topo && L.p == 1 && L.m == 1 && L.E <= kSmallRootElems &&
+           !(learned && lv.size() == 1);
+  }
+  int root_small(double* u, const double* g, bool* breakdown, bool wait) {
+    Level& L = lv[0];
+    const DegTab& t = *L.bk[0].t;
+    SmallRootArgs a;
+    a.E = L.E; a.n = opt.root_max_iter; a.check = kCheck; a.rtol = opt.root_rtol;
+    a.project = opt.null_space; a.kappa = opt.kappa; a.inv_wend = t.inv_wend;
+    a.u = u; a.g = g;
+    a.G = L.G; a.WJ = opt.kappa != 0.0 ? L.WJ : nullptr; a.pen = L.pen; a.D = t.D;
+    a.nbr = L.nbr; a.bc = L.bc; a.nb27 = L.nb27; a.var = L.var;
+    a.gco = L.gco; a.S = t.S; a.lam = t.lam; a.W = t.W;
+    a.scal = scal;
+    small_root(a, nrhs, st);
+    if (!wait || fixed_root()) return opt.root_max_iter;
+    std::vector<double> h((size_t)8 * nrhs);
+    HIPC(hipMemcpyAsync(h.data(), scal, h.size() * sizeof(double), hipMemcpyDeviceToHost, st));
+    HIPC(hipStreamSynchronize(st));
+    int it = 0;
+    for (int k = 0; k < nrhs; ++k) {
+      if (h[k * 8 + 4] != 0.0 && breakdown) *breakdown = true;
+      it = std::max(it, (int)h[k * 8 + 5]);
+    }
+    return it;
+  }
+
+  // wait: the iteration count and a breakdown are wanted (the one-launch solve needs no
+  // synchronisation otherwise)
+  int root_solve(double* u, const double* g, bool* breakdown, bool wait = false) {
+    if (small_root_fits()) return root_small(u, g, breakdown, wait);
     Level& L = lv[0];
     if (fixed_root()) return scg<double>(L, u, g, opt.root_max_iter, {}, breakdown);
     residual(L, u, g, L.r);
@@ -2469,7 +2504,7 @@ dgfas_status dgfas_root_solve(dgfas_solver sv, double* u, const double* g, int32
   Solver* s = S_(sv);
   need(u, "u"); need(g, "g");
   bool bd = false;
-  const int it = s->root_solve(u, g, &bd);
+  const int it = s->root_solve(u, g, &bd, true);
   HIPC(hipStreamSynchronize(s->st));
   if (iters) *iters = it;
   if (bd) throw Error(DGFAS_EBREAKDOWN, "SCG breakdown in the root solve");
