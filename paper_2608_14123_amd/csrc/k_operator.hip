@@ -535,8 +535,11 @@ sipg_batched_kernel(OpArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, i
   }
 }
 
-int stage_tiles(int stage, int p, int nel, int nrhs) {
-  if (stage == kStageSolve) return nel * nrhs;
+int stage_tiles(int stage, int p, int nel, int nrhs, int pmax) {
+  if (stage == kStageSolve) {   // degrees 1 and 2: as many subdomains as columns fit the workgroup
+    const int spw = p <= 2 ? stage_threads(kStageSolve, pmax) / ((p + 3) * (p + 3)) : 1;
+    return (nel * nrhs + spw - 1) / spw;
+  }
   const int epb = stage == kStageOp ? ColShape<2>::ES[p + 1] : kAddElems[p + 1];   // elements per tile
   return ((nel + epb - 1) / epb) * nrhs;
 }

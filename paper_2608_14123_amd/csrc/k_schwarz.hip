@@ -258,9 +258,175 @@ __device__ __forceinline__ void schwarz_tile(SchwarzArgs<T> a, const int lbr, Sz
   }
 }
 
-// Small subdomains (n <= 3, ns^3 <= 125): one thread per tile point, looping over the
-// points when the workgroup is narrower than the tile; the three directions' tables are
-// staged in LDS.  The contraction order and arithmetic are those of schwarz_tile.
+// Small subdomains (n <= 3, ns <= 5): several to a workgroup, one thread per xi_3 column as in
+// schwarz_tile, with its order of contractions and its arithmetic.  The eigenvector tables of all 16 side
+// variants (at most 3.2 KB) are staged in LDS, as the subdomains of a wavefront may differ; a
+// wavefront whose subdomains share their variants takes the scalar cache instead.  One subdomain a
+// workgroup with one thread per point read 12 values from LDS per point and contraction step and
+// waited alone for its neighbour ids (p = 1: 26.7 us, now 15.8; p = 2: 59 us, now 30.7 on 32^3).
+// Below kPackElems subdomains the chip is not full and one thread per point (schwarz_point_tile) has the
+// shorter chain: 7.5 us both on 16^3, 4.9 against 7.2 us on 4^3 (p = 1).
+constexpr int kPackElems = 4096;   // elements of a launch from which several subdomains share a workgroup
+
+template <int N, int M, typename T, int THR>
+struct PackSmem {
+  static constexpr int NS = N + 2 * M, NS2 = NS * NS, SPW = THR / NS2, ROW = NS | 1;
+  T tile[SPW][NS2 * ROW];
+  T S[16][NS2 + 1];
+  T lam[16][NS];
+  T W[16][NS];
+  int nb[SPW][27];
+  int off[27];
+};
+
+// Subdomains lbt SPW .. of the list (element in the list, right-hand side fastest)
+template <int N, int M, typename T, int THR>
+__device__ __forceinline__ void schwarz_pack_tile(const SchwarzArgs<T>& a, const int lbt, PackSmem<N, M, T, THR>& sm,
+                                                   const int tid) {
+  using Sm = PackSmem<N, M, T, THR>;
+  constexpr int NS = Sm::NS, NS2 = Sm::NS2, SPW = Sm::SPW, ROW = Sm::ROW;
+  constexpr Regions<N, M> R{};
+  const int sd = tid / NS2, c = tid - sd * NS2, c1 = c % NS, c2 = c / NS;
+  const int lbr = lbt * SPW + sd;
+  bool act = sd < SPW && lbr < a.nel * a.nrhs;
+  const int li = act ? lbr / a.nrhs : 0, rhs = act ? lbr - li * a.nrhs : 0;
+  const int e = a.elist ? a.elist[li] : li;
+  if (a.sel && !a.sel[e]) act = false;
+  const T* __restrict__ r = a.r + (int64_t)rhs * a.ndof;
+  T* __restrict__ z = a.z + (int64_t)rhs * a.ndof;
+  T* __restrict__ O = a.O + (int64_t)rhs * a.nin;
+  const int v0 = a.var[(int64_t)e * 3 + 0], v1 = a.var[(int64_t)e * 3 + 1], v2 = a.var[(int64_t)e * 3 + 2];
+  for (int t = tid; t < 16 * NS2; t += THR) sm.S[t / NS2][t % NS2] = a.S[t];
+  for (int t = tid; t < 16 * NS; t += THR) {
+    sm.lam[t / NS][t % NS] = a.lam[t];
+    sm.W[t / NS][t % NS] = a.W[t];
+  }
+  if (M > 0 && tid < 27) sm.off[tid] = R.off[tid];
+  // the neighbour ids go through LDS, so that they do not wait for the variants
+  if (sd < SPW)
+    for (int t = c; t < 27; t += NS2) sm.nb[sd][t] = a.nb27[(int64_t)e * 27 + t];
+  const T g0 = a.gco[(int64_t)e * 4 + 0], g1 = a.gco[(int64_t)e * 4 + 1];
+  const T g2 = a.gco[(int64_t)e * 4 + 2], g3 = a.gco[(int64_t)e * 4 + 3];
+  __syncthreads();
+  const int m1 = tile_map<N, M>(v0, c1), m2 = act ? tile_map<N, M>(v1, c2) : -1;
+  const bool in = m1 >= 0 && m2 >= 0;
+  const int l1 = m1 & 63, l2 = m2 & 63, l12 = l2 * N + l1;
+  int nb[3] = {-1, -1, -1};   // the elements the column crosses; absent ones: zeros, no scatter
+  if (in) {
+#pragma unroll
+    for (int d3 = 0; d3 < 3; ++d3) nb[d3] = sm.nb[sd][d3 * 9 + (m2 >> 6) * 3 + (m1 >> 6)];
+    if (a.deg) {
+#pragma unroll
+      for (int d3 = 0; d3 < 3; ++d3)
+        if (nb[d3] >= 0 && a.deg[nb[d3]] != N - 1) nb[d3] = -1;   // another degree: zero fill, no scatter
+    }
+  }
+  T line[NS];
+#pragma unroll
+  for (int s3 = 0; s3 < NS; ++s3) {
+    const int m3 = tile_map<N, M>(v2, s3);
+    const int q = m3 < 0 ? -1 : (m3 < 64 ? nb[0] : (m3 < 128 ? nb[1] : nb[2]));
+    line[s3] = 0;
+    if (q >= 0) line[s3] = r[elem_base<N>(a, q) + l12 + (m3 & 63) * (N * N)];
+  }
+  // out_c = sum_q (S^T or S)[c][q] in_q with the table of variant v: v packs the three variants, `dir`
+  // selects one, so that one test per wavefront covers all three
+  const int code = (v0 * 16 + v1) * 16 + v2, first = __builtin_amdgcn_readfirstlane(code);
+  const bool same = __ballot(code != first) == 0;
+  const int u0 = first >> 8, u1 = (first >> 4) & 15, u2 = first & 15;
+  auto apply = [&](int v, int u, bool tr, T (&t)[NS]) {
+    T o[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) o[k] = 0;
+    if (same) {
+      const ctab<T> S = table(a.S) + u * NS2;
+#pragma unroll
+      for (int k = 0; k < NS; ++k)
+#pragma unroll
+        for (int q = 0; q < NS; ++q) o[k] += S[tr ? q * NS + k : k * NS + q] * t[q];
+    } else {
+      const T* __restrict__ S = sm.S[v];
+#pragma unroll
+      for (int k = 0; k < NS; ++k)
+#pragma unroll
+        for (int q = 0; q < NS; ++q) o[k] += S[tr ? q * NS + k : k * NS + q] * t[q];
+    }
+#pragma unroll
+    for (int k = 0; k < NS; ++k) t[k] = o[k];
+  };
+  T* const tile = sm.tile[sd < SPW ? sd : 0];
+  const bool own = sd < SPW;
+  auto load = [&](int at, int stride) {
+#pragma unroll
+    for (int q = 0; q < NS; ++q) line[q] = tile[at + q * stride];
+  };
+  auto store = [&](int at, int stride) {
+    if (own) {
+#pragma unroll
+      for (int q = 0; q < NS; ++q) tile[at + q * stride] = line[q];
+    }
+    __syncthreads();
+  };
+  const int z0 = c2 * ROW + c1, sz = NS * ROW;   // column (s1 = c1, s2 = c2) along xi_3
+  const int y0 = c2 * NS * ROW + c1;             // line (s1 = c1, s3 = c2) along xi_2
+  const int x0 = c * ROW;                        // line (s2 = c1, s3 = c2) along xi_1
+  apply(v2, u2, true, line);
+  store(z0, sz);
+  load(y0, ROW);
+  apply(v1, u1, true, line);
+  store(y0, ROW);
+  load(x0, 1);
+  apply(v0, u0, true, line);
+  const T base = g0 + g2 * sm.lam[v1][c1] + g3 * sm.lam[v2][c2];
+#pragma unroll
+  for (int k = 0; k < NS; ++k) line[k] = line[k] / (base + g1 * sm.lam[v0][k]);
+  apply(v0, u0, false, line);
+  store(x0, 1);
+  load(y0, ROW);
+  apply(v1, u1, false, line);
+  store(y0, ROW);
+  load(z0, sz);
+  apply(v2, u2, false, line);
+  // weighted scatter: own part to z, overlap parts into the receivers' inboxes
+  if (!in) return;
+  const int d1 = (m1 >> 6) - 1, d2 = (m2 >> 6) - 1;
+  const T w12 = sm.W[v0][c1] * sm.W[v1][c2];
+  const int x1 = d1 ? M : N, x2 = d2 ? M : N;
+  const int cc = (d2 < 0 ? l2 - (N - M) : l2) * x1 + (d1 < 0 ? l1 - (N - M) : l1);
+#pragma unroll
+  for (int s3 = 0; s3 < NS; ++s3) {
+    const int m3 = tile_map<N, M>(v2, s3);
+    if (m3 < 0) continue;
+    const int l3 = m3 & 63, d3 = (m3 >> 6) - 1;
+    const int q = d3 < 0 ? nb[0] : (d3 == 0 ? nb[1] : nb[2]);
+    if (q < 0) continue;
+    T t = line[s3];
+    if (a.corr) t += (T)(a.cscale[e] * (double)a.corr[(int64_t)e * (NS2 * NS) + (s3 * NS + c2) * NS + c1]);
+    T val = a.unweighted ? t : w12 * sm.W[v2][s3] * t;
+    const int64_t gi = elem_base<N>(a, q) + l12 + l3 * (N * N);
+    if (a.cinv && !a.unweighted) val *= a.cinv[gi];   // normalised weight
+    if (d1 == 0 && d2 == 0 && d3 == 0) {
+      if (a.mode == 0) z[gi] = val;
+      else z[gi] += val;
+    } else {
+      const int rr = (1 - d3) * 9 + (1 - d2) * 3 + (1 - d1);      // direction from the receiver back to e
+      const int c3 = d3 < 0 ? l3 - (N - M) : l3;
+      O[inbox_base<N, M>(a, q) + sm.off[rr] + c3 * x2 * x1 + cc] = val;
+    }
+  }
+}
+
+template <int N, int M, typename T, int THR>
+__global__ void __launch_bounds__(THR) schwarz_pack_kernel(SchwarzArgs<T> a) {
+  using Sm = PackSmem<N, M, T, THR>;
+  __shared__ Sm sm;
+  const int lbt = xcd_block((a.nel * a.nrhs + Sm::SPW - 1) / Sm::SPW);
+  if (lbt < 0) return;
+  schwarz_pack_tile<N, M, T, THR>(a, lbt, sm, threadIdx.x);
+}
+
+// The same with one subdomain a workgroup and one thread per tile point, for few subdomains; the three
+// directions' tables are staged in LDS.
 template <int N, int M, typename T>
 struct PtSmem {
   static constexpr int NS = N + 2 * M, NT = NS * NS * NS;
@@ -274,9 +440,8 @@ struct PtSmem {
 };
 
 template <int N, int M, typename T>
-__device__ __forceinline__ void schwarz_point_tile(SchwarzArgs<T> a, const int lbr, PtSmem<N, M, T>& sm,
-                                                   const int nthr, int tid_in = -1) {
-  constexpr int NS = N + 2 * M, NT = NS * NS * NS, MAXP = (NT + 63) / 64;
+__device__ __forceinline__ void schwarz_point_tile(SchwarzArgs<T> a, const int lbr, PtSmem<N, M, T>& sm) {
+  constexpr int NS = N + 2 * M, NT = NS * NS * NS, MAXP = 1, nthr = (NT + 63) / 64 * 64;
   constexpr Regions<N, M> R{};
   const int li = lbr / a.nrhs, rhs = lbr - li * a.nrhs;
   const int e = a.elist ? a.elist[li] : li;
@@ -284,7 +449,7 @@ __device__ __forceinline__ void schwarz_point_tile(SchwarzArgs<T> a, const int l
   a.r += (int64_t)rhs * a.ndof;
   a.z += (int64_t)rhs * a.ndof;
   a.O += (int64_t)rhs * a.nin;
-  const int tid = tid_in >= 0 ? tid_in : (int)threadIdx.x;
+  const int tid = threadIdx.x;
   const int vv[3] = {__builtin_amdgcn_readfirstlane(a.var[(int64_t)e * 3 + 0]),
                      __builtin_amdgcn_readfirstlane(a.var[(int64_t)e * 3 + 1]),
                      __builtin_amdgcn_readfirstlane(a.var[(int64_t)e * 3 + 2])};
@@ -328,10 +493,10 @@ __device__ __forceinline__ void schwarz_point_tile(SchwarzArgs<T> a, const int l
     if (q < NT) sm.tile[q] = v[pp];
   }
   __syncthreads();
-  // six contractions: xi_1 S1^T, xi_2 S2^T, xi_3 S3^T and 1/D, xi_3 S3, xi_2 S2, xi_1 S1
+  // six contractions: xi_3 S3^T, xi_2 S2^T, xi_1 S1^T and 1/D, xi_1 S1, xi_2 S2, xi_3 S3
 #pragma unroll 1
   for (int step = 0; step < 6; ++step) {
-    const int dir = step < 3 ? step : 5 - step;
+    const int dir = step < 3 ? 2 - step : step - 3;
     const bool tr = step < 3;
 #pragma unroll
     for (int pp = 0; pp < MAXP; ++pp) {
@@ -344,7 +509,7 @@ __device__ __forceinline__ void schwarz_point_tile(SchwarzArgs<T> a, const int l
       T acc = 0;
 #pragma unroll
       for (int k = 0; k < NS; ++k) acc += (tr ? sm.S[dir][k * NS + c] : sm.S[dir][c * NS + k]) * sm.tile[q0 + k * stride];
-      if (step == 2) acc = acc / (g0 + g1 * sm.lam[0][s[0]] + g2 * sm.lam[1][s[1]] + g3 * sm.lam[2][s[2]]);
+      if (step == 2) acc = acc / (g0 + g2 * sm.lam[1][s[1]] + g3 * sm.lam[2][s[2]] + g1 * sm.lam[0][s[0]]);
       v[pp] = acc;
     }
     __syncthreads();
@@ -391,7 +556,7 @@ schwarz_point_kernel(SchwarzArgs<T> a) {
   __shared__ PtSmem<N, M, T> sm;
   const int lbr = xcd_block(a.nel * a.nrhs);
   if (lbr < 0) return;
-  schwarz_point_tile<N, M, T>(a, lbr, sm, blockDim.x);
+  schwarz_point_tile<N, M, T>(a, lbr, sm);
 }
 
 template <int N>
@@ -414,35 +579,42 @@ schwarz_solve_kernel(SchwarzArgs<T> a) {
 template <int N, int M, typename T>
 struct AddSmem {
   static constexpr int OSZ = Regions<N, M>{}.size;
-  T box[AddShape<N>::EPB][OSZ];   // the elements' inboxes
+  static constexpr bool STAGED = N > 3;   // else the few entries are read where they are
+  T box[STAGED ? AddShape<N>::EPB : 1][STAGED ? OSZ : 1];   // the elements' inboxes
   int sOff[27];
   double red[2][AddShape<N>::THREADS / 64];   // per-wavefront partial sums of the fused dot products
 };
 
-// Sum of the neighbours' overlap contributions to node (l0, l1, l2) from the element's staged
+// Sum of the neighbours' overlap contributions to node (l0, l1, l2) from the element's
 // inbox, in a fixed order (the up to 7 regions whose overlap covers the node).  Inbox regions of
 // absent neighbours stay zero.
 template <int N, int M, typename T>
 __device__ __forceinline__ T inbox_sum(const T* box, const int* sOff, const int (&l)[3], const int (&od)[3]) {
-  T acc = 0;
+  // every load is issued unconditionally (invalid ones read entry 0 and are masked), so that none
+  // waits on another
+  T vals[7];
+  bool ok[7];
 #pragma unroll
   for (int bits = 1; bits < 8; ++bits) {
     const bool valid = ((bits & 1) == 0 || od[0] != 0) && ((bits & 2) == 0 || od[1] != 0) &&
                        ((bits & 4) == 0 || od[2] != 0);
-    if (!valid) continue;
     const int dd[3] = {(bits & 1) ? od[0] : 0, (bits & 2) ? od[1] : 0, (bits & 4) ? od[2] : 0};
     const int r = (dd[2] + 1) * 9 + (dd[1] + 1) * 3 + (dd[0] + 1);
     const int c1 = dd[0] > 0 ? l[0] - (N - M) : l[0];
     const int c2 = dd[1] > 0 ? l[1] - (N - M) : l[1];
     const int c3 = dd[2] > 0 ? l[2] - (N - M) : l[2];
     const int x1 = dd[0] ? M : N, x2 = dd[1] ? M : N;
-    acc += box[sOff[r] + (c3 * x2 + c2) * x1 + c1];
+    ok[bits - 1] = valid;
+    vals[bits - 1] = box[valid ? sOff[r] + (c3 * x2 + c2) * x1 + c1 : 0];
   }
+  T acc = 0;
+#pragma unroll
+  for (int t = 0; t < 7; ++t) acc += ok[t] ? vals[t] : T(0);
   return acc;
 }
 
-// z[node] += sum of the neighbours' overlap contributions in the element's own inbox.  The inbox
-// is one contiguous block and comes into LDS with coalesced loads: reading the up to 7 entries of
+// z[node] += sum of the neighbours' overlap contributions in the element's own inbox.  From n = 4 on the
+// inbox, one contiguous block, comes into LDS with coalesced loads: reading the up to 7 entries of
 // every node from global memory kept the address units busy 79 % of the launch (32^3, p = 7:
 // 128 us with seven loads a node, 104 from LDS with one node a thread, now 73; with the dot
 // products 154, now 123, in FP32 122, now 71).  With dotz set, also the tile's sums of z dr and
@@ -464,10 +636,12 @@ __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr
     return a.elist ? a.elist[li] : li;
   };
   T in[NB], z0[KN];
+  if constexpr (AddSmem<N, M, T>::STAGED) {
 #pragma unroll
-  for (int k = 0; k < NB; ++k) {
-    const int t = min(tid + k * THR, EPB * OSZ - 1), le = t / OSZ;
-    in[k] = a.O[inbox_base<N, M>(a, element(le)) + (t - le * OSZ)];
+    for (int k = 0; k < NB; ++k) {
+      const int t = min(tid + k * THR, EPB * OSZ - 1), le = t / OSZ;
+      in[k] = a.O[inbox_base<N, M>(a, element(le)) + (t - le * OSZ)];
+    }
   }
   int64_t gi[KN];
   double rv[KN], r0v[KN];
@@ -483,9 +657,11 @@ __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr
       if (a.dr0) r0v[k] = (double)a.dr0[ri];
     }
   }
+  if constexpr (AddSmem<N, M, T>::STAGED) {
 #pragma unroll
-  for (int k = 0; k < NB; ++k)
-    if (tid + k * THR < EPB * OSZ) sm.box[(tid + k * THR) / OSZ][(tid + k * THR) % OSZ] = in[k];
+    for (int k = 0; k < NB; ++k)
+      if (tid + k * THR < EPB * OSZ) sm.box[(tid + k * THR) / OSZ][(tid + k * THR) % OSZ] = in[k];
+  }
   __syncthreads();
   double pz = 0, pz2 = 0;
 #pragma unroll
@@ -499,7 +675,8 @@ __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr
     for (int d = 0; d < 3; ++d) od[d] = (l[d] < M) ? -1 : ((l[d] >= N - M) ? 1 : 0);
     T zv = z0[k];
     if (od[0] != 0 || od[1] != 0 || od[2] != 0) {
-      zv += inbox_sum<N, M, T>(sm.box[le], sm.sOff, l, od);
+      if constexpr (AddSmem<N, M, T>::STAGED) zv += inbox_sum<N, M, T>(sm.box[le], sm.sOff, l, od);
+      else zv += inbox_sum<N, M, T>(a.O + inbox_base<N, M>(a, element(le)), sm.sOff, l, od);
       a.z[gi[k]] = zv;
     }
     pz += (double)zv * rv[k];
@@ -695,8 +872,12 @@ template void mark_subdomains<double>(int, int, const SchwarzArgs<double>&, cons
 template <int N, int M, typename T>
 void launch_schwarz(const SchwarzArgs<T>& a, hipStream_t st) {
   if constexpr (N <= 3) {
-    constexpr int NS = N + 2 * M, THR = (NS * NS * NS + 63) / 64 * 64;
-    hipLaunchKernelGGL((schwarz_point_kernel<N, M, T>), dim3(xcd_grid(a.nel * a.nrhs)), dim3(THR), 0, st, a);
+    constexpr int NS = N + 2 * M, NT = (NS * NS * NS + 63) / 64 * 64, SPW = PackSmem<N, M, T, 256>::SPW;
+    if (a.nel >= kPackElems)
+      hipLaunchKernelGGL((schwarz_pack_kernel<N, M, T, 256>), dim3(xcd_grid((a.nel * a.nrhs + SPW - 1) / SPW)), dim3(256),
+                         0, st, a);
+    else
+      hipLaunchKernelGGL((schwarz_point_kernel<N, M, T>), dim3(xcd_grid(a.nel * a.nrhs)), dim3(NT), 0, st, a);
   } else {
     hipLaunchKernelGGL((schwarz_solve_kernel<N, M, T>), dim3(xcd_grid(a.nel * a.nrhs)), dim3(SzShape<N, M>::THREADS),
                        0, st, a);
@@ -748,12 +929,13 @@ void schwarz_overlap_add(int p, int m, const SchwarzArgs<T>& a, hipStream_t st) 
 
 // ---------------------------------------------------------------------------
 // Batched launches over the degree buckets of a mixed-degree level (overlap m = 1).
-template <typename T, int N>
+template <typename T, int N, int THR>
 constexpr size_t sz_smem_upto() {
   if constexpr (N < 2) {
     return 0;
   } else {
-    constexpr size_t a = N <= 3 ? sizeof(PtSmem<N, 1, T>) : sizeof(SzSmem<N, 1, T>), b = sz_smem_upto<T, N - 1>();
+    constexpr size_t a = N <= 3 ? sizeof(PackSmem<N, 1, T, THR>) : sizeof(SzSmem<N, 1, T>),
+                     b = sz_smem_upto<T, N - 1, THR>();
     return a > b ? a : b;
   }
 }
@@ -761,7 +943,8 @@ constexpr size_t sz_smem_upto() {
 template <int NMAX, typename T, bool PERSIST>
 __global__ void __launch_bounds__((SzShape<NMAX, 1>::THREADS))
 schwarz_batched_kernel(SchwarzArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, int ntiles) {
-  __shared__ __align__(16) char smem[sz_smem_upto<T, NMAX>()];
+  constexpr int THR = SzShape<NMAX, 1>::THREADS;
+  __shared__ __align__(16) char smem[sz_smem_upto<T, NMAX, THR>()];
   // tiles dealt round-robin over the XCDs (the hardware order): the work list runs from the
   // largest degree to the smallest, and contiguous ranges per XCD would leave one XCD all
   // the large tiles.  The persistent form strides through the list, with a barrier between
@@ -785,7 +968,7 @@ schwarz_batched_kernel(SchwarzArgs<T> a, const BucketDesc<T>* __restrict__ bd, i
     switch (bd[k].p) {
 #define DGFAS_SZB(P)                                                                                  \
   case P:                                                                                             \
-    if constexpr (P + 1 <= 3) schwarz_point_tile<P + 1, 1, T>(x, lbr, *reinterpret_cast<PtSmem<P + 1, 1, T>*>(smem), blockDim.x, tid); \
+    if constexpr (P + 1 <= 3) schwarz_pack_tile<P + 1, 1, T, THR>(x, lbr, *reinterpret_cast<PackSmem<P + 1, 1, T, THR>*>(smem), tid < 0 ? (int)threadIdx.x : tid); \
     else if constexpr (P + 1 <= NMAX) schwarz_tile<P + 1, 1, T>(x, lbr, *reinterpret_cast<SzSmem<P + 1, 1, T>*>(smem), tid); \
     break;
       DGFAS_SZB(1) DGFAS_SZB(2) DGFAS_SZB(3) DGFAS_SZB(4) DGFAS_SZB(5) DGFAS_SZB(6) DGFAS_SZB(7) DGFAS_SZB(8)

@@ -68,8 +68,9 @@ enum { kStageOp = 0, kStageSolve = 1, kStageAdd = 2 };
 // elements per 256-thread tile of the overlap add by n = p + 1: two to four nodes a thread, so that
 // a tile's loads overlap and its dot products are reduced once for that many nodes
 constexpr int kAddElems[10] = {0, 0, 32, 9, 4, 2, 4, 2, 2, 1};
-// tiles per bucket of each stage (elements per tile times right-hand sides)
-int stage_tiles(int stage, int p, int nel, int nrhs);
+// tiles per bucket of each stage (element blocks times right-hand sides); pmax: largest degree of the
+// batched launch (subdomain solves only)
+int stage_tiles(int stage, int p, int nel, int nrhs, int pmax = 8);
 // workgroup size of the batched kernel of a stage for largest degree pmax
 int stage_threads(int stage, int pmax);
 template <typename T>

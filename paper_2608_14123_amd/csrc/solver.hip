@@ -1259,7 +1259,7 @@ void build_level(Solver& s, Level& L, const std::vector<int>& deg, const double*
       x.elist = y.elist = b.elist;
       for (int sg = 0; sg < 3; ++sg) {
         x.tile0[sg] = y.tile0[sg] = t0[sg];
-        t0[sg] += stage_tiles(sg, b.p, b.nel, s.nrhs);
+        t0[sg] += stage_tiles(sg, b.p, b.nel, s.nrhs, L.p);
       }
       x.D = t.D; x.S = t.S; x.ST = t.ST; x.lam = t.lam; x.W = t.W; x.map1d = t.map1d; x.inv_wend = t.inv_wend;
       y.D = t.D32; y.S = t.S32; y.ST = t.ST32; y.lam = t.lam32; y.W = t.W32; y.map1d = t.map1d;
