@@ -34,12 +34,13 @@ struct OpShape {
 // 768-thread workgroup of which one fits a CU; here a p = 8 element takes 243 threads and three
 // fit.  H and EPB were measured on 20^3 to 32^3 elements (one thread per node, chosen; best of the
 // other splits): p = 1: 9.1, 7.2; 7.5 us, p = 2: 26.1, 22.3; 23.2, p = 3: 55.6, 40.5; 41.4,
-// p = 4: 126.8, 111.5; 121.6, p = 5: 47.3, 37.9; 39.9, p = 6: 96.6, 70.1; 72.5,
-// p = 7: 418, 377; 387, p = 8: 215, 141; 236.
-template <int N>
+// p = 4: 126.8, 111.5; 121.6, p = 5: 47.3, 37.9; 39.9, p = 7: 418, 377; 387, p = 8: 215, 141; 236.
+// p = 6 takes one node a thread: 96, 76 us on 20^3, 5.3, 5.1 on 4^3, where four threads a column take 72
+// and 6.0; the batched launches (WIDE) take four there, which fit their 256-thread workgroups.
+template <int N, bool WIDE = false>
 struct ColShape {
   static constexpr int N2 = N * N, N3 = N * N * N;
-  static constexpr int HS[10] = {0, 0, 2, 3, 2, 3, 6, 4, 4, 3}, ES[10] = {0, 0, 8, 7, 4, 3, 1, 1, 1, 1};
+  static constexpr int HS[10] = {0, 0, 2, 3, 2, 3, 6, WIDE ? 4 : 7, 4, 3}, ES[10] = {0, 0, 8, 7, 4, 3, 1, 1, 1, 1};
   static constexpr int H = HS[N], EPB = ES[N];
   static constexpr int KPT = (N + H - 1) / H;
   static constexpr int NR = (6 + H - 1) / H;                   // face tasks per thread
@@ -56,16 +57,16 @@ struct alignas(2 * sizeof(T)) FacePair {
   T a, s;   // a face node's row term without the own flux, and its lifting weight
 };
 
-template <int N, typename T>
+template <int N, typename T, bool WIDE = false>
 struct OpSmem {
-  using S = ColShape<N>;
+  using S = ColShape<N, WIDE>;
   T sD[S::N2];                         // D[i][m] at i N + m
   T su[S::EPB][S::V3];                 // u, then the xi_1 fluxes
   T sTr[S::EPB][6 * S::F2 > S::V3 ? 6 * S::F2 : S::V3];   // neighbour traces, then the xi_2 fluxes
   T sF2[S::EPB][S::V3];                // xi_3 fluxes
   FacePair<T> sAS[S::EPB][6][S::N2];
   T sQ[S::EPB][6];                     // weight of the own flux in the row term: interior 1/2, Dirichlet 1
-  double red[4];                       // per-wavefront partial sums of the fused dot product
+  double red[6];                       // per-wavefront partial sums of the fused dot product
 };
 
 // nothing is moved across: keeps the loads of a later stage (and their registers) out of an
@@ -123,8 +124,8 @@ __device__ __forceinline__ int face_axis_first(int phi) { return phi < 4 ? 2 : 1
 // MIXED: a level of several degrees (per-element offsets; a neighbour of another degree is left
 // to the mortar face kernel, whose terms the tile adds through OpArgs::fmapE).
 template <int N, typename T, bool ORIENT, bool MIXED, bool WIDE>
-__device__ __forceinline__ void sipg_tile(const OpArgs<T>& a, const int lbr, OpSmem<N, T>& sm, const int tid) {
-  using S = ColShape<N>;
+__device__ __forceinline__ void sipg_tile(const OpArgs<T>& a, const int lbr, OpSmem<N, T, WIDE>& sm, const int tid) {
+  using S = ColShape<N, WIDE>;
   constexpr int N2 = S::N2, N3 = S::N3, H = S::H, KPT = S::KPT, NR = S::NR, TE = S::TE, EPB = S::EPB;
   constexpr int P = S::P, F2 = S::F2;
   constexpr bool CUT = N % H != 0;      // the last slice is short
@@ -480,7 +481,7 @@ constexpr size_t op_smem_upto() {
   if constexpr (N < 2) {
     return 0;
   } else {
-    constexpr size_t a = sizeof(OpSmem<N, T>), b = op_smem_upto<T, N - 1>();
+    constexpr size_t a = sizeof(OpSmem<N, T, true>), b = op_smem_upto<T, N - 1>();
     return a > b ? a : b;
   }
 }
@@ -489,7 +490,7 @@ constexpr int op_threads_upto() {
   if constexpr (N < 2) {
     return 0;
   } else {
-    constexpr int a = ColShape<N>::THREADS, b = op_threads_upto<N - 1>();
+    constexpr int a = ColShape<N, true>::THREADS, b = op_threads_upto<N - 1>();
     return a > b ? a : b;
   }
 }
@@ -518,7 +519,7 @@ sipg_batched_kernel(OpArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, i
     switch (bd[k].p) {
 #define DGFAS_OPB(P)                                                                        \
   case P:                                                                                   \
-    if constexpr (P + 1 <= NMAX) sipg_tile<P + 1, T, false, true, true>(x, lbr, *reinterpret_cast<OpSmem<P + 1, T>*>(smem), tid); \
+    if constexpr (P + 1 <= NMAX) sipg_tile<P + 1, T, false, true, true>(x, lbr, *reinterpret_cast<OpSmem<P + 1, T, true>*>(smem), tid); \
     break;
       DGFAS_OPB(1) DGFAS_OPB(2) DGFAS_OPB(3) DGFAS_OPB(4) DGFAS_OPB(5) DGFAS_OPB(6) DGFAS_OPB(7) DGFAS_OPB(8)
 #undef DGFAS_OPB
