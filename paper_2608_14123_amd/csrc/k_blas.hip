@@ -11,16 +11,37 @@
 
 namespace dgfas {
 
-// one thread per output of the wider of the first two contraction steps (the inputs and the
-// last step's outputs are taken in loops), so that neither a restriction nor a prolongation
-// idles most of a workgroup sized for its largest array
+// A thread contracts whole lines: each of the three directions reads NI values of a line, gives NO,
+// and the transfer's rows come through the scalar cache, so that a value crosses LDS once a step and
+// no thread reads a row of T.  With NI >= NO the first step takes the lines along z straight from
+// global memory (consecutive threads, consecutive nodes), then x, then y; with NI < NO it takes y
+// first and z last, so that the larger array, then the output, is the one accessed node by node.
+// Old output values (accumulate) are loaded before the first step.  Bound: the two arrays' bytes.
+// EPB elements fill about 256 threads with the longer of the first and the last step's lines.
+// Measured, p = 8 <-> 4 on 24^3: restriction 52.0 -> 15.5 us (6.1 TB/s), prolongation 57.8 -> 27.7 (7.0
+// TB/s) against one node a thread; 5 <-> 2 on 24^3: 11.1 -> 4.6, 13.9 -> 7.8; 6^3 grids 4.3 as before.
 template <int NI, int NO>
 struct TrShape {
-  static constexpr int W1 = NI * NI * NO, W2 = NI * NO * NO, W3 = NO * NO * NO;
-  static constexpr int M3 = W1 > W2 ? W1 : W2;
-  static constexpr int EPB = (M3 >= 256) ? 1 : (256 / M3);
-  static constexpr int THREADS = ((EPB * M3 + 63) / 64) * 64;
+  static constexpr int ML = NI > NO ? NI * NI : NO * NO;
+  static constexpr int EPB = 256 / ML;
+  static constexpr int THREADS = ((EPB * ML + 63) / 64) * 64;
+  static constexpr int RI = NI | 1, RO = NO | 1;   // odd rows: lines along a row read without bank conflicts
 };
+
+template <typename T>
+using trtab = const __attribute__((address_space(4))) T*;
+
+// out[m] = sum_k T[m][k] in[k], T at a uniform address
+template <int NI, int NO, typename T>
+__device__ __forceinline__ void line_transfer(trtab<T> Tm, const T (&in)[NI], T (&out)[NO]) {
+#pragma unroll
+  for (int m = 0; m < NO; ++m) {
+    T s = 0;
+#pragma unroll
+    for (int k = 0; k < NI; ++k) s += Tm[m * NI + k] * in[k];
+    out[m] = s;
+  }
+}
 
 // Element e of the launch list, sub-block s = rhs * ncomp + comp:
 //   in  + rhs * stride_in  + off_in[e]  * ncomp + comp * NI^3
@@ -29,54 +50,79 @@ template <int NI, int NO, typename T>
 __global__ void __launch_bounds__((TrShape<NI, NO>::THREADS))
 tensor3_kernel(XferArgs<T> a) {
   using S = TrShape<NI, NO>;
-  constexpr int M3 = S::M3, EPB = S::EPB, I3 = NI * NI * NI, O3 = NO * NO * NO;
+  constexpr int EPB = S::EPB, RI = S::RI, RO = S::RO, I3 = NI * NI * NI, O3 = NO * NO * NO;
+  constexpr int L1 = NI * NI, L2 = NI * NO, L3 = NO * NO;
+  constexpr bool ZFIRST = NI >= NO;
   const int nsub = a.nrhs * a.ncomp;
   const int lbs = xcd_block(((a.nel + EPB - 1) / EPB) * nsub);
   if (lbs < 0) return;
   const int lb = lbs / nsub, sub = lbs - lb * nsub;
   const int rhs = sub / a.ncomp, comp = sub - rhs * a.ncomp;
-  const int tid = threadIdx.x;
-  const int le = tid / M3, q = tid - le * M3;
-  const int li = lb * EPB + le;
-  const bool act = le < EPB && li < a.nel;
-  const int e = act ? (a.elist ? a.elist[li] : li) : 0;
-  const int64_t ib = (int64_t)rhs * a.stride_in + (a.off_in ? a.off_in[e] : (int64_t)e * I3) * a.ncomp +
-                     (int64_t)comp * I3;
-  const int64_t ob = (int64_t)rhs * a.stride_out + (a.off_out ? a.off_out[e] : (int64_t)e * O3) * a.ncomp +
-                     (int64_t)comp * O3;
-  __shared__ T sT[NO * NI];
-  __shared__ T s0[EPB][NI * NI * NI];
-  __shared__ T s1[EPB][NI * NI * NO];
-  __shared__ T s2[EPB][NI * NO * NO];
-  for (int t = tid; t < NO * NI; t += S::THREADS) sT[t] = a.Tm[t];
-  if (act) {
-    for (int t = q; t < I3; t += M3) {
-      T v = a.in[ib + t];
-      if (a.in2) v -= a.in2[ib + t];
-      s0[le][t] = v;
+  const int tid = threadIdx.x, here = min(EPB, a.nel - lb * EPB);   // elements of this block
+  const trtab<T> Tm = (trtab<T>)(uintptr_t)a.Tm;
+  __shared__ T s1[EPB][L2 * RI];   // first step's lines laid down along x: row (z or k, j or b), RI a row
+  __shared__ T s2[EPB][L2 * RO];
+  auto elem = [&](int le) {
+    const int li = lb * EPB + le;
+    return a.elist ? a.elist[li] : li;
+  };
+  const int le3 = tid / L3, q3 = tid - le3 * L3;
+  const bool act3 = le3 < here && tid < EPB * L3;
+  // node (c, b, a) of the last step's line: c (ZFIRST) or b, and a fixed
+  const int o3 = ZFIRST ? (q3 / NO) * L3 + q3 % NO : q3;
+  constexpr int so = ZFIRST ? NO : L3;
+  T old[NO];
+  T* op = nullptr;
+  if (act3) {
+    const int e = elem(le3);
+    op = a.out + (int64_t)rhs * a.stride_out + (a.off_out ? a.off_out[e] : (int64_t)e * O3) * a.ncomp +
+         (int64_t)comp * O3 + o3;
+    if (a.accumulate) {
+#pragma unroll
+      for (int m = 0; m < NO; ++m) old[m] = op[m * so];
+    }
+  }
+  {
+    const int le = tid / L1, q = tid - le * L1;
+    if (le < here && tid < EPB * L1) {
+      const int e = elem(le);
+      constexpr int si = ZFIRST ? NI * NI : NI;
+      const int hi = q / NI, x = q - hi * NI;
+      const int64_t ib = (int64_t)rhs * a.stride_in + (a.off_in ? a.off_in[e] : (int64_t)e * I3) * a.ncomp +
+                         (int64_t)comp * I3 + (ZFIRST ? q : hi * NI * NI + x);
+      T v[NI], w[NO];
+#pragma unroll
+      for (int k = 0; k < NI; ++k) v[k] = a.in[ib + k * si];
+      if (a.in2) {
+#pragma unroll
+        for (int k = 0; k < NI; ++k) v[k] -= a.in2[ib + k * si];
+      }
+      line_transfer<NI, NO, T>(Tm, v, w);
+#pragma unroll
+      for (int m = 0; m < NO; ++m) s1[le][(ZFIRST ? m * NI + hi : hi * NO + m) * RI + x] = w[m];
     }
   }
   __syncthreads();
-  if (act && q < NI * NI * NO) {   // [k][j][a]
-    const int x = q % NO, j = (q / NO) % NI, k = q / (NO * NI);
-    T s = 0;
-    for (int i = 0; i < NI; ++i) s += sT[x * NI + i] * s0[le][(k * NI + j) * NI + i];
-    s1[le][q] = s;
+  {
+    const int le = tid / L2, q = tid - le * L2;
+    if (le < here && tid < EPB * L2) {
+      T v[NI], w[NO];
+#pragma unroll
+      for (int k = 0; k < NI; ++k) v[k] = s1[le][q * RI + k];
+      line_transfer<NI, NO, T>(Tm, v, w);
+#pragma unroll
+      for (int m = 0; m < NO; ++m) s2[le][q * RO + m] = w[m];
+    }
   }
   __syncthreads();
-  if (act && q < NI * NO * NO) {   // [k][b][a]
-    const int x = q % NO, y = (q / NO) % NO, k = q / (NO * NO);
-    T s = 0;
-    for (int j = 0; j < NI; ++j) s += sT[y * NI + j] * s1[le][(k * NI + j) * NO + x];
-    s2[le][q] = s;
-  }
-  __syncthreads();
-  for (int qq = q; act && qq < O3; qq += M3) {   // [c][b][a]
-    const int x = qq % NO, y = (qq / NO) % NO, c = qq / (NO * NO);
-    T s = 0;
-    for (int k = 0; k < NI; ++k) s += sT[c * NI + k] * s2[le][(k * NO + y) * NO + x];
-    const int64_t o = ob + qq;
-    a.out[o] = a.accumulate ? a.out[o] + s : s;
+  if (act3) {
+    const int hi = q3 / NO, x = q3 - hi * NO;
+    T v[NI], w[NO];
+#pragma unroll
+    for (int k = 0; k < NI; ++k) v[k] = s2[le3][(ZFIRST ? hi * NI + k : k * NO + hi) * RO + x];
+    line_transfer<NI, NO, T>(Tm, v, w);
+#pragma unroll
+    for (int m = 0; m < NO; ++m) op[m * so] = a.accumulate ? old[m] + w[m] : w[m];
   }
 }
 
