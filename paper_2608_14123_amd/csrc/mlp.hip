@@ -40,14 +40,14 @@ T* mal(size_t n) {
 
 Mlp::~Mlp() {
   if (st) hipStreamSynchronize(st);
-  void* ps[] = {w, wb, w3p, g, m, v, Xb, H1b, H2b, dYb, G2b, G1b, H1, H2, G2, G1, part, kws};
+  void* ps[] = {w, wb, w3p, g, m, v, Xb, H1b, H2b, dYb, G2b, G1b, H1, H2, part, kws};
   for (void* p : ps)
     if (p) hipFree(p);
 }
 
 void Mlp::reserve(int rows) {
   if (rows <= cap) return;
-  void* ps[] = {Xb, H1b, H2b, dYb, G2b, G1b, H1, H2, G2, G1, kws};
+  void* ps[] = {Xb, H1b, H2b, dYb, G2b, G1b, H1, H2, kws};
   MHIP(hipStreamSynchronize(st));
   for (void* p : ps)
     if (p) hipFree(p);
@@ -61,8 +61,6 @@ void Mlp::reserve(int rows) {
   G1b = mal<uint16_t>((size_t)rows * h);
   H1 = mal<float>((size_t)rows * h);
   H2 = mal<float>((size_t)rows * h);
-  G2 = mal<float>((size_t)rows * h);
-  G1 = mal<float>((size_t)rows * h);
   // up to 16 K-slices of the largest weight gradient (at most 2^24 floats: a slice count the
   // cap cannot hold falls back to fewer slices)
   const int64_t mn = std::max<int64_t>((int64_t)(in + 1) * h,
@@ -95,12 +93,10 @@ double Mlp::backward(const float* X, const float* T, int rows, float* Y) {
   // output row is the bias gradient, which follows the weights in the parameter array
   // layer 3
   gemm_bf16(h + 1, out, rows, H2b, 1, h, dYb, outp, 1, g + off_w3, nullptr, nullptr, 0, 0, st, kws, kws_cap, 1);
-  gemm_bf16(rows, h, out, dYb, outp, 1, w3p, 1, outp, G2, nullptr, nullptr, 0, 0, st, kws, kws_cap);
-  relu_back((int64_t)rows * h, G2, H2, G2b, st);
+  gemm_bf16(rows, h, out, dYb, outp, 1, w3p, 1, outp, nullptr, G2b, nullptr, 0, 0, st, kws, kws_cap, 0, H2);
   // layer 2
   gemm_bf16(h + 1, h, rows, H1b, 1, h, G2b, h, 1, g + off_w2, nullptr, nullptr, 0, 0, st, kws, kws_cap, 1);
-  gemm_bf16(rows, h, h, G2b, h, 1, wb + off_w2, 1, h, G1, nullptr, nullptr, 0, 0, st);
-  relu_back((int64_t)rows * h, G1, H1, G1b, st);
+  gemm_bf16(rows, h, h, G2b, h, 1, wb + off_w2, 1, h, nullptr, G1b, nullptr, 0, 0, st, nullptr, 0, 0, H1);
   // layer 1
   gemm_bf16(in + 1, h, rows, Xb, 1, in, G1b, h, 1, g + off_w1, nullptr, nullptr, 0, 0, st, kws, kws_cap, 1);
   std::vector<double> hp(nb);

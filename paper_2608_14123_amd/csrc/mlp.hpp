@@ -8,15 +8,14 @@ namespace dgfas {
 void cast_bf16(int64_t n, const float* x, uint16_t* y, hipStream_t st);
 // ws (ws_cap floats, may be null) holds the K-slice partial sums of a split-K launch; with
 // ones_row, row M - 1 of A is a row of ones (A itself has M - 1 rows), so that row M - 1 of C
-// holds the column sums of B
+// holds the column sums of B; gate (M x N, may be null) zeroes C where it is not positive
 void gemm_bf16(int M, int N, int K, const uint16_t* A, int64_t sam, int64_t sak, const uint16_t* B, int64_t sbk,
                int64_t sbn, float* C, uint16_t* Cb, const float* bias, int relu, int accumulate, hipStream_t st,
-               float* ws = nullptr, int64_t ws_cap = 0, int ones_row = 0);
+               float* ws = nullptr, int64_t ws_cap = 0, int ones_row = 0, const float* gate = nullptr);
 int gemm_splits(int M, int N, int K, int64_t ws_cap);
 void mse_grad(int64_t n, int cols, int ldb, const float* Y, const float* T, float scale, uint16_t* dYb, double* part,
               int nblocks, hipStream_t st);
 void pad_rows(int rows, int cols, int ldd, const uint16_t* src, uint16_t* dst, hipStream_t st);
-void relu_back(int64_t n, float* G, const float* H, uint16_t* Gb, hipStream_t st);
 void adam(int64_t n, float* w, const float* g, float* m, float* v, uint16_t* wb, float lr, float b1, float b2,
           float eps, float c1, float c2, hipStream_t st);
 
@@ -37,7 +36,7 @@ struct Mlp {
   // activations for up to cap rows
   int cap = 0;
   uint16_t *Xb = nullptr, *H1b = nullptr, *H2b = nullptr, *dYb = nullptr, *G2b = nullptr, *G1b = nullptr;
-  float *H1 = nullptr, *H2 = nullptr, *G2 = nullptr, *G1 = nullptr;   // dYb: rows of pitch outp
+  float *H1 = nullptr, *H2 = nullptr;   // dYb: rows of pitch outp
   double* part = nullptr;
   float* kws = nullptr;      // split-K partial sums
   int64_t kws_cap = 0;
