@@ -37,17 +37,22 @@ struct Mlp {
   int cap = 0;
   uint16_t *Xb = nullptr, *H1b = nullptr, *H2b = nullptr, *dYb = nullptr, *G2b = nullptr, *G1b = nullptr;
   float *H1 = nullptr, *H2 = nullptr;   // dYb: rows of pitch outp
-  double* part = nullptr;
+  double* part = nullptr;    // loss partials, and their page-locked host copy
+  double* hpart = nullptr;
+  float* Yw = nullptr;       // a training batch's outputs, ycap rows
+  int ycap = 0;
   float* kws = nullptr;      // split-K partial sums
   int64_t kws_cap = 0;
 
   void reserve(int rows);
+  float* outputs(int rows);
   void refresh_bf16();
   void refresh_w3p();
   // Y = f(X), X [rows][in] FP32 (device), Y [rows][out] FP32 (device)
   void forward(const float* X, int rows, float* Y);
-  // forward + MSE loss (mean over rows*out) + gradient into g; returns the loss (synchronises)
-  double backward(const float* X, const float* T, int rows, float* Y);
+  // forward + MSE loss (mean over rows*out) + gradient into g, copied to grad if that is set; returns
+  // the loss (synchronises)
+  double backward(const float* X, const float* T, int rows, float* grad);
   ~Mlp();
 };
 
