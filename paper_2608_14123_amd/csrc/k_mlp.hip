@@ -1,7 +1,7 @@
 // K6: the learned subdomain correction -- a 3-layer MLP with BF16 weights and FP32
 // accumulation, trained on the GPU.  GEMMs run on the CDNA matrix cores
-// (v_mfma_f32_16x16x16bf16_1k); element-wise work (bias, ReLU and its derivative,
-// MSE gradient, column sums, Adam) runs in plain kernels.
+// (v_mfma_f32_16x16x16bf16_1k), with bias, ReLU and its derivative in their last pass and
+// column sums as a row of ones; the casts, the MSE gradient and Adam run in plain kernels.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -46,7 +46,7 @@ void cast_bf16(int64_t n, const float* x, uint16_t* y, hipStream_t st) {
 // C[m][n] = sum_k A(m,k) B(k,n) (+ bias[n]) (ReLU) with A(m,k) = A[m*sam + k*sak],
 // B(k,n) = B[k*sbk + n*sbn] in BF16, C row-major FP32 (ldc = N) and optionally a BF16 copy.
 // Workgroup: 4 wavefronts, 64x64 tile, each wavefront 32x32 = 2x2 MFMA 16x16 blocks;
-// K advances 32 per LDS stage.  Out-of-range rows/columns/k are zero-filled.
+// K advances 64 per LDS stage.  Out-of-range rows/columns/k are zero-filled.
 // Split K: with P set, slice z = blockIdx.z takes k in [z kper, (z + 1) kper) and writes its
 // raw sum to P[z][m][n]; splitk_reduce adds the slices in order and applies the epilogue, so
 // the result does not depend on scheduling.
