@@ -77,6 +77,10 @@ __device__ __forceinline__ ctab<T> table(const T* p) {
   return (ctab<T>)(uintptr_t)p;
 }
 
+// table in LDS
+template <typename T>
+using ltab = const __attribute__((address_space(3))) T*;
+
 // out_c = sum_q Mt[c][q] in_q for a tile line in registers
 template <int NS, typename T>
 __device__ __forceinline__ T line_row(ctab<T> Mt, int c, const T (&in)[NS]) {
@@ -345,7 +349,10 @@ __device__ __forceinline__ void schwarz_pack_tile(const SchwarzArgs<T>& a, const
 #pragma unroll
         for (int q = 0; q < NS; ++q) o[k] += S[tr ? q * NS + k : k * NS + q] * t[q];
     } else {
-      const T* __restrict__ S = sm.S[v];
+      // one address in a register, the entries at offsets from it: left to itself the compiler adds a
+      // constant per entry and keeps these constants in registers over a persistent loop
+      ltab<T> S = (ltab<T>)sm.S[v];
+      asm volatile("" : "+v"(S));
 #pragma unroll
       for (int k = 0; k < NS; ++k)
 #pragma unroll
@@ -940,8 +947,15 @@ constexpr size_t sz_smem_upto() {
   }
 }
 
+// The persistent form is held to six waves per SIMD in FP64 and eight in FP32: without a bound the
+// compiler keeps the constants of every degree's tile live over the loop (162 and 132 registers, three
+// waves; 27^3 hp front, largest degree 8: application 162 us, now 110; FP32 smoothing of four steps 1.62 ms,
+// now 1.43).  The one-tile form has no loop and needs no bound (96 us).
+template <typename T, bool PERSIST>
+constexpr int kSolveWaves = !PERSIST ? 1 : sizeof(T) == 8 ? 6 : 8;
+
 template <int NMAX, typename T, bool PERSIST>
-__global__ void __launch_bounds__((SzShape<NMAX, 1>::THREADS))
+__global__ void __launch_bounds__((SzShape<NMAX, 1>::THREADS), (kSolveWaves<T, PERSIST>))
 schwarz_batched_kernel(SchwarzArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, int ntiles) {
   constexpr int THR = SzShape<NMAX, 1>::THREADS;
   __shared__ __align__(16) char smem[sz_smem_upto<T, NMAX, THR>()];
