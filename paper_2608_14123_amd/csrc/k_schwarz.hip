@@ -3,13 +3,12 @@
 //   (A~_s)^-1 = (S3 x S2 x S1) D^-1 (S3^T x S2^T x S1^T),
 //   D = g0 + g1 lam1_i + g2 lam2_j + g3 lam3_k.
 //
-// schwarz_solve: one workgroup per subdomain.  The NS^3 tile (NS = N + 2M, smaller
-// variants zero-padded) is gathered from the element and its 26 neighbours into
-// LDS; each 1D contraction runs with one thread per tile line, the other two
-// tile indices spread over the threads so that LDS accesses are unit-stride
-// across the wavefront (the xi_1 lines use an odd row pitch).  The weighted own
-// part goes straight to z (or is added to u), the weighted overlap parts go to a
-// per-element overlap buffer.
+// schwarz_solve: the NS^3 tile (NS = N + 2M, smaller variants zero-padded) is gathered from the
+// element and its 26 neighbours, contracted along xi_3, xi_2, xi_1, divided, and contracted back.  Three forms:
+// one workgroup per subdomain and a thread per tile line (schwarz_tile, n >= 4), several small subdomains
+// to a workgroup with a thread per line (schwarz_pack_tile), one small subdomain and a thread per point
+// (schwarz_point_tile).  The weighted own part goes straight to z (or is added to u), the weighted overlap
+// parts go to a per-element overlap buffer.
 // schwarz_overlap_add: gather form of the scatter, z[node] += contributions of
 // the neighbours' subdomains in a fixed order -- deterministic, no atomics.
 #include <type_traits>
@@ -433,7 +432,9 @@ __global__ void __launch_bounds__(THR) schwarz_pack_kernel(SchwarzArgs<T> a) {
 }
 
 // The same with one subdomain a workgroup and one thread per tile point, for few subdomains; the three
-// directions' tables are staged in LDS.
+// directions' tables are staged in LDS.  Bound: the chain of gather, six contractions and scatter.  A thread
+// finds its position, its element and its node once and keeps its value in a register: finding them anew
+// in every step took 5.3 us on 4^3 and 6.0 on 12^3 at p = 1, now 4.6 and 5.2 (p = 2: 5.4 and 7.4, now 4.6 and 6.5).
 template <int N, int M, typename T>
 struct PtSmem {
   static constexpr int NS = N + 2 * M, NT = NS * NS * NS;
@@ -448,7 +449,8 @@ struct PtSmem {
 
 template <int N, int M, typename T>
 __device__ __forceinline__ void schwarz_point_tile(SchwarzArgs<T> a, const int lbr, PtSmem<N, M, T>& sm) {
-  constexpr int NS = N + 2 * M, NT = NS * NS * NS, MAXP = 1, nthr = (NT + 63) / 64 * 64;
+  using Sm = PtSmem<N, M, T>;
+  constexpr int NS = Sm::NS, NT = Sm::NT, THR = (NT + 63) / 64 * 64;
   constexpr Regions<N, M> R{};
   const int li = lbr / a.nrhs, rhs = lbr - li * a.nrhs;
   const int e = a.elist ? a.elist[li] : li;
@@ -456,104 +458,75 @@ __device__ __forceinline__ void schwarz_point_tile(SchwarzArgs<T> a, const int l
   a.r += (int64_t)rhs * a.ndof;
   a.z += (int64_t)rhs * a.ndof;
   a.O += (int64_t)rhs * a.nin;
-  const int tid = threadIdx.x;
+  const int q = threadIdx.x;
   const int vv[3] = {__builtin_amdgcn_readfirstlane(a.var[(int64_t)e * 3 + 0]),
                      __builtin_amdgcn_readfirstlane(a.var[(int64_t)e * 3 + 1]),
                      __builtin_amdgcn_readfirstlane(a.var[(int64_t)e * 3 + 2])};
-  for (int t = tid; t < 3 * NS * NS; t += nthr) {
-    const int d = t / (NS * NS), q = t - d * NS * NS;
-    sm.S[d][q] = a.S[vv[d] * NS * NS + q];
+  for (int t = q; t < 3 * NS * NS; t += THR) {
+    const int d = t / (NS * NS), k = t - d * NS * NS;
+    sm.S[d][k] = a.S[vv[d] * NS * NS + k];
   }
-  for (int t = tid; t < 3 * NS; t += nthr) {
-    const int d = t / NS, q = t - d * NS;
-    sm.lam[d][q] = a.lam[vv[d] * NS + q];
-    sm.W[d][q] = a.W[vv[d] * NS + q];
-    sm.map[d][q] = a.map1d[vv[d] * NS + q];
+  for (int t = q; t < 3 * NS; t += THR) {
+    const int d = t / NS, k = t - d * NS;
+    sm.lam[d][k] = a.lam[vv[d] * NS + k];
+    sm.W[d][k] = a.W[vv[d] * NS + k];
+    sm.map[d][k] = a.map1d[vv[d] * NS + k];
   }
-  if (tid < 27) {
-    int nb = a.nb27[(int64_t)e * 27 + tid];
+  if (q < 27) {
+    int nb = a.nb27[(int64_t)e * 27 + q];
     if (nb >= 0 && a.deg && a.deg[nb] != N - 1) nb = -1;   // another degree: zero fill, no scatter
-    sm.nb[tid] = nb;
-    sm.off[tid] = R.off[tid];
+    sm.nb[q] = nb;
+    sm.off[q] = R.off[q];
   }
   const T g0 = a.gco[(int64_t)e * 4 + 0], g1 = a.gco[(int64_t)e * 4 + 1];
   const T g2 = a.gco[(int64_t)e * 4 + 2], g3 = a.gco[(int64_t)e * 4 + 3];
   __syncthreads();
-  T v[MAXP];
   // gather r_s = R_s r
-#pragma unroll
-  for (int pp = 0; pp < MAXP; ++pp) {
-    const int q = tid + pp * nthr;
-    v[pp] = 0;
-    if (q < NT) {
-      const int s1 = q % NS, s2 = (q / NS) % NS, s3 = q / (NS * NS);
-      const int m1 = sm.map[0][s1], m2 = sm.map[1][s2], m3 = sm.map[2][s3];
-      if (m1 >= 0 && m2 >= 0 && m3 >= 0) {
-        const int src = sm.nb[(m3 >> 6) * 9 + (m2 >> 6) * 3 + (m1 >> 6)];
-        if (src >= 0) v[pp] = a.r[elem_base<N>(a, src) + ((m3 & 63) * N + (m2 & 63)) * N + (m1 & 63)];
-      }
-    }
-  }
-#pragma unroll
-  for (int pp = 0; pp < MAXP; ++pp) {
-    const int q = tid + pp * nthr;
-    if (q < NT) sm.tile[q] = v[pp];
-  }
+  const bool act = q < NT;   // threads beyond the tile only meet at the barriers
+  const int s1 = q % NS, s2 = (q / NS) % NS, s3 = act ? q / (NS * NS) : 0;
+  const int m1 = sm.map[0][s1], m2 = sm.map[1][s2], m3 = sm.map[2][s3];
+  const bool in = act && m1 >= 0 && m2 >= 0 && m3 >= 0;
+  const int src = in ? sm.nb[(m3 >> 6) * 9 + (m2 >> 6) * 3 + (m1 >> 6)] : -1;
+  const int local = ((m3 & 63) * N + (m2 & 63)) * N + (m1 & 63);
+  T v = 0;
+  if (src >= 0) v = a.r[elem_base<N>(a, src) + local];
+  if (act) sm.tile[q] = v;
   __syncthreads();
   // six contractions: xi_3 S3^T, xi_2 S2^T, xi_1 S1^T and 1/D, xi_1 S1, xi_2 S2, xi_3 S3
 #pragma unroll 1
   for (int step = 0; step < 6; ++step) {
     const int dir = step < 3 ? 2 - step : step - 3;
     const bool tr = step < 3;
+    const int c = dir == 0 ? s1 : dir == 1 ? s2 : s3, stride = dir == 0 ? 1 : (dir == 1 ? NS : NS * NS);
+    if (act) {
+      const T* line = sm.tile + (q - c * stride);
+      v = 0;
 #pragma unroll
-    for (int pp = 0; pp < MAXP; ++pp) {
-      const int q = tid + pp * nthr;
-      if (q >= NT) continue;
-      const int s[3] = {q % NS, (q / NS) % NS, q / (NS * NS)};
-      const int c = s[dir];
-      const int stride = dir == 0 ? 1 : (dir == 1 ? NS : NS * NS);
-      const int q0 = q - c * stride;
-      T acc = 0;
-#pragma unroll
-      for (int k = 0; k < NS; ++k) acc += (tr ? sm.S[dir][k * NS + c] : sm.S[dir][c * NS + k]) * sm.tile[q0 + k * stride];
-      if (step == 2) acc = acc / (g0 + g2 * sm.lam[1][s[1]] + g3 * sm.lam[2][s[2]] + g1 * sm.lam[0][s[0]]);
-      v[pp] = acc;
+      for (int k = 0; k < NS; ++k) v += (tr ? sm.S[dir][k * NS + c] : sm.S[dir][c * NS + k]) * line[k * stride];
+      if (step == 2) v = v / (g0 + g2 * sm.lam[1][s2] + g3 * sm.lam[2][s3] + g1 * sm.lam[0][s1]);
     }
+    if (step == 5) break;
     __syncthreads();
-#pragma unroll
-    for (int pp = 0; pp < MAXP; ++pp) {
-      const int q = tid + pp * nthr;
-      if (q < NT) sm.tile[q] = v[pp];
-    }
+    if (act) sm.tile[q] = v;
     __syncthreads();
   }
   // weighted scatter: own part to z, overlap parts into the receivers' inboxes
-#pragma unroll
-  for (int pp = 0; pp < MAXP; ++pp) {
-    const int q = tid + pp * nthr;
-    if (q >= NT) continue;
-    const int s1 = q % NS, s2 = (q / NS) % NS, s3 = q / (NS * NS);
-    const int m1 = sm.map[0][s1], m2 = sm.map[1][s2], m3 = sm.map[2][s3];
-    if (m1 < 0 || m2 < 0 || m3 < 0) continue;
-    T t = sm.tile[q];
-    if (a.corr) t += (T)(a.cscale[e] * (double)a.corr[(int64_t)e * NT + q]);
-    T val = a.unweighted ? t : sm.W[0][s1] * sm.W[1][s2] * sm.W[2][s3] * t;
-    const int d1 = (m1 >> 6) - 1, d2 = (m2 >> 6) - 1, d3 = (m3 >> 6) - 1;
-    const int l1 = m1 & 63, l2 = m2 & 63, l3 = m3 & 63;
-    if (d1 == 0 && d2 == 0 && d3 == 0) {
-      const int64_t gi = elem_base<N>(a, e) + (l3 * N + l2) * N + l1;
-      if (a.cinv && !a.unweighted) val *= a.cinv[gi];   // normalised weight
-      if (a.mode == 0) a.z[gi] = val;
-      else a.z[gi] += val;
-    } else {
-      const int dest = sm.nb[(d3 + 1) * 9 + (d2 + 1) * 3 + (d1 + 1)];
-      if (dest < 0) continue;
-      if (a.cinv && !a.unweighted) val *= a.cinv[elem_base<N>(a, dest) + (l3 * N + l2) * N + l1];
-      const int r = (1 - d3) * 9 + (1 - d2) * 3 + (1 - d1);      // direction from dest back to e
-      const int c1 = d1 < 0 ? l1 - (N - M) : l1, c2 = d2 < 0 ? l2 - (N - M) : l2, c3 = d3 < 0 ? l3 - (N - M) : l3;
-      const int x1 = d1 ? M : N, x2 = d2 ? M : N;
-      a.O[inbox_base<N, M>(a, dest) + sm.off[r] + (c3 * x2 + c2) * x1 + c1] = val;
-    }
+  if (src < 0) return;
+  T t = v;
+  if (a.corr) t += (T)(a.cscale[e] * (double)a.corr[(int64_t)e * NT + q]);
+  T val = a.unweighted ? t : sm.W[0][s1] * sm.W[1][s2] * sm.W[2][s3] * t;
+  const int64_t gi = elem_base<N>(a, src) + local;
+  if (a.cinv && !a.unweighted) val *= a.cinv[gi];   // normalised weight
+  const int d1 = (m1 >> 6) - 1, d2 = (m2 >> 6) - 1, d3 = (m3 >> 6) - 1;
+  const int l1 = m1 & 63, l2 = m2 & 63, l3 = m3 & 63;
+  if (d1 == 0 && d2 == 0 && d3 == 0) {
+    if (a.mode == 0) a.z[gi] = val;
+    else a.z[gi] += val;
+  } else {
+    const int r = (1 - d3) * 9 + (1 - d2) * 3 + (1 - d1);      // direction from the receiver back to e
+    const int c1 = d1 < 0 ? l1 - (N - M) : l1, c2 = d2 < 0 ? l2 - (N - M) : l2, c3 = d3 < 0 ? l3 - (N - M) : l3;
+    const int x1 = d1 ? M : N, x2 = d2 ? M : N;
+    a.O[inbox_base<N, M>(a, src) + sm.off[r] + (c3 * x2 + c2) * x1 + c1] = val;
   }
 }
 
