@@ -267,9 +267,13 @@ __device__ __forceinline__ void schwarz_tile(SchwarzArgs<T> a, const int lbr, Sz
 // wavefront whose subdomains share their variants takes the scalar cache instead.  One subdomain a
 // workgroup with one thread per point read 12 values from LDS per point and contraction step and
 // waited alone for its neighbour ids (p = 1: 26.7 us, now 15.8; p = 2: 59 us, now 30.7 on 32^3).
-// Below kPackElems subdomains the chip is not full and one thread per point (schwarz_point_tile) has the
-// shorter chain: 7.5 us both on 16^3, 4.9 against 7.2 us on 4^3 (p = 1).
-constexpr int kPackElems = 4096;   // elements of a launch from which several subdomains share a workgroup
+// Below kPackSubs subdomains (elements times right-hand sides) the chip is not full and one thread per point
+// (schwarz_point_tile) has the shorter chain.  Point and pack form, p = 1 and 2 with one overlap layer:
+//   FP64  2744: 5.9, 6.5 and 8.3, 9.4 us   4096: 6.7, 6.7 and 10.1, 10.0   5832: 8.3, 7.5 and 12.3, 11.4
+//   FP32  4096: 5.7, 6.5 and 7.4, 8.4      5832: 6.7, 6.9 and 9.8, 8.9     8000: 7.5, 7.1 and 11.4, 10.1
+// Four right-hand sides on 10^3 elements meet alike (6.6, 6.9 and 10.0, 9.9); both forms give the same bits.
+template <typename T>
+constexpr int64_t kPackSubs = sizeof(T) == 8 ? 4096 : 5632;
 
 template <int N, int M, typename T, int THR>
 struct PackSmem {
@@ -853,7 +857,7 @@ template <int N, int M, typename T>
 void launch_schwarz(const SchwarzArgs<T>& a, hipStream_t st) {
   if constexpr (N <= 3) {
     constexpr int NS = N + 2 * M, NT = (NS * NS * NS + 63) / 64 * 64, SPW = PackSmem<N, M, T, 256>::SPW;
-    if (a.nel >= kPackElems)
+    if ((int64_t)a.nel * a.nrhs >= kPackSubs<T>)
       hipLaunchKernelGGL((schwarz_pack_kernel<N, M, T, 256>), dim3(xcd_grid((a.nel * a.nrhs + SPW - 1) / SPW)), dim3(256),
                          0, st, a);
     else
