@@ -306,7 +306,7 @@ __global__ void __launch_bounds__(kThreads) small_root_kernel(SmallRootArgs a) {
   sum2(sm, 0, rr, o);
   const double stop = a.rtol > 0 ? a.rtol * sqrt(rr) : 0.0;
   int it = 0;
-  bool bad = false, conv = false;
+  bool bad = a.rtol > 0 && isnan(rr), conv = false;   // with a stop of NaN there is no iteration to find it
   double gamma = 0, p = 0, r0 = 0;
   if (!(a.rtol > 0) || stop > 0) {
     if (node) sm.v[tid] = r;

@@ -777,10 +777,13 @@ struct Solver {
     HIPC(hipMemcpyAsync(h.data(), scal, h.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     HIPC(hipStreamSynchronize(st));
     int it = 0;
+    bool bad = false;
     for (int k = 0; k < nrhs; ++k) {
-      if (h[k * 8 + 4] != 0.0 && breakdown) *breakdown = true;
+      bad = bad || h[k * 8 + 4] != 0.0;
       it = std::max(it, (int)h[k * 8 + 5]);
     }
+    // as in the general path, there is no solve to break down where no right-hand side iterates
+    if (it > 0 && bad && breakdown) *breakdown = true;
     return it;
   }
 
