@@ -48,11 +48,15 @@ Mlp::~Mlp() {
 
 void Mlp::reserve(int rows) {
   if (rows <= cap) return;
-  void* ps[] = {Xb, H1b, H2b, dYb, G2b, G1b, H1, H2, kws};
   MHIP(hipStreamSynchronize(st));
-  for (void* p : ps)
+  // nothing is held until all of it is: an allocation that fails leaves an empty workspace
+  cap = 0;
+  kws_cap = 0;
+  auto drop = [](auto*& p) {
     if (p) hipFree(p);
-  cap = rows;
+    p = nullptr;
+  };
+  drop(Xb); drop(H1b); drop(H2b); drop(dYb); drop(G2b); drop(G1b); drop(H1); drop(H2); drop(kws);
   Xb = mal<uint16_t>((size_t)rows * in);
   H1b = mal<uint16_t>((size_t)rows * h);
   H2b = mal<uint16_t>((size_t)rows * h);
@@ -68,6 +72,7 @@ void Mlp::reserve(int rows) {
                                        std::max<int64_t>((int64_t)(h + 1) * h, (int64_t)(h + 1) * out));
   kws_cap = std::min<int64_t>(16 * mn, (int64_t)1 << 24);
   kws = mal<float>((size_t)kws_cap);
+  cap = rows;
 }
 
 // a training batch's outputs, kept until a larger batch or the network's end: an allocation a call
