@@ -549,10 +549,18 @@ struct AddShape {
   static constexpr int KN = (EPB * N3 + THREADS - 1) / THREADS;   // nodes per thread
 };
 
+// Waves per SIMD asked of the compiler: eight (64 registers), or what the tiles leave room for in the CU's
+// 160 KB of LDS: in FP64 at p = 8 seven with one overlap layer and six with two or three.  The two-wave
+// workgroups hide each other's gather and barriers (32^3, p = 7: 180 us at six waves, 174 at eight; 20^3,
+// p = 8, m = 1 to 3: 59, 100 and 159 us with a bound of eight, 58, 97 and 158 with these).
 template <int N, int M, typename T>
-// eight waves per SIMD (64 registers, where the larger tiles have room in LDS): the two-wave
-// workgroups hide each other's gather and barriers (32^3, p = 7: 180 us at six waves, 174 at eight)
-__global__ void __launch_bounds__((SzShape<N, M>::THREADS), 8)
+constexpr int solve_waves() {
+  const int w = 163840 / (int)sizeof(SzSmem<N, M, T>) * (SzShape<N, M>::THREADS / 64) / 4;
+  return w < 8 ? w : 8;
+}
+
+template <int N, int M, typename T>
+__global__ void __launch_bounds__((SzShape<N, M>::THREADS), (solve_waves<N, M, T>()))
 schwarz_solve_kernel(SchwarzArgs<T> a) {
   __shared__ SzSmem<N, M, T> sm;
   const int lbr = xcd_block(a.nel * a.nrhs);
