@@ -543,9 +543,9 @@ schwarz_point_kernel(SchwarzArgs<T> a) {
   schwarz_point_tile<N, M, T>(a, lbr, sm);
 }
 
-template <int N>
+template <int N, int EPB>
 struct AddShape {
-  static constexpr int N3 = N * N * N, EPB = kAddElems[N], THREADS = 256;
+  static constexpr int N3 = N * N * N, THREADS = 256;
   static constexpr int KN = (EPB * N3 + THREADS - 1) / THREADS;   // nodes per thread
 };
 
@@ -568,13 +568,13 @@ schwarz_solve_kernel(SchwarzArgs<T> a) {
   schwarz_tile<N, M, T>(a, lbr, sm);
 }
 
-template <int N, int M, typename T>
+template <int N, int M, typename T, int EPB = kAddElems[N]>
 struct AddSmem {
   static constexpr int OSZ = Regions<N, M>{}.size;
   static constexpr bool STAGED = N > 3;   // else the few entries are read where they are
-  T box[STAGED ? AddShape<N>::EPB : 1][STAGED ? OSZ : 1];   // the elements' inboxes
+  T box[STAGED ? EPB : 1][STAGED ? OSZ : 1];   // the elements' inboxes
   int sOff[27];
-  double red[2][AddShape<N>::THREADS / 64];   // per-wavefront partial sums of the fused dot products
+  double red[2][AddShape<N, EPB>::THREADS / 64];   // per-wavefront partial sums of the fused dot products
 };
 
 // Sum of the neighbours' overlap contributions to node (l0, l1, l2) from the element's
@@ -611,10 +611,12 @@ __device__ __forceinline__ T inbox_sum(const T* box, const int* sOff, const int 
 // 128 us with seven loads a node, 104 from LDS with one node a thread, now 73; with the dot
 // products 154, now 123, in FP32 122, now 71).  With dotz set, also the tile's sums of z dr and
 // z (dr - dr0) over every node (deterministic order).
-template <int N, int M, typename T>
-__device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr, AddSmem<N, M, T>& sm, int tid_in = -1) {
-  using Sh = AddShape<N>;
-  constexpr int N3 = Sh::N3, EPB = Sh::EPB, KN = Sh::KN, THR = Sh::THREADS, OSZ = AddSmem<N, M, T>::OSZ;
+template <int N, int M, typename T, int EPB>
+__device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr, AddSmem<N, M, T, EPB>& sm,
+                                                 int tid_in = -1) {
+  using Sh = AddShape<N, EPB>;
+  using Sm = AddSmem<N, M, T, EPB>;
+  constexpr int N3 = Sh::N3, KN = Sh::KN, THR = Sh::THREADS, OSZ = Sm::OSZ;
   constexpr int NB = (EPB * OSZ + THR - 1) / THR;
   constexpr Regions<N, M> R{};
   const int lb = lbr / a.nrhs, rhs = lbr - lb * a.nrhs;
@@ -628,7 +630,7 @@ __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr
     return a.elist ? a.elist[li] : li;
   };
   T in[NB], z0[KN];
-  if constexpr (AddSmem<N, M, T>::STAGED) {
+  if constexpr (Sm::STAGED) {
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int t = min(tid + k * THR, EPB * OSZ - 1), le = t / OSZ;
@@ -649,7 +651,7 @@ __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr
       if (a.dr0) r0v[k] = (double)a.dr0[ri];
     }
   }
-  if constexpr (AddSmem<N, M, T>::STAGED) {
+  if constexpr (Sm::STAGED) {
 #pragma unroll
     for (int k = 0; k < NB; ++k)
       if (tid + k * THR < EPB * OSZ) sm.box[(tid + k * THR) / OSZ][(tid + k * THR) % OSZ] = in[k];
@@ -667,7 +669,7 @@ __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr
     for (int d = 0; d < 3; ++d) od[d] = (l[d] < M) ? -1 : ((l[d] >= N - M) ? 1 : 0);
     T zv = z0[k];
     if (od[0] != 0 || od[1] != 0 || od[2] != 0) {
-      if constexpr (AddSmem<N, M, T>::STAGED) zv += inbox_sum<N, M, T>(sm.box[le], sm.sOff, l, od);
+      if constexpr (Sm::STAGED) zv += inbox_sum<N, M, T>(sm.box[le], sm.sOff, l, od);
       else zv += inbox_sum<N, M, T>(a.O + inbox_base<N, M>(a, element(le)), sm.sOff, l, od);
       a.z[gi[k]] = zv;
     }
@@ -695,14 +697,13 @@ __device__ __forceinline__ void overlap_add_tile(SchwarzArgs<T> a, const int lbr
   }
 }
 
-template <int N, int M, typename T>
-__global__ void __launch_bounds__(AddShape<N>::THREADS)
+template <int N, int M, typename T, int EPB>
+__global__ void __launch_bounds__((AddShape<N, EPB>::THREADS))
 schwarz_overlap_add_kernel(SchwarzArgs<T> a) {
-  using Sh = AddShape<N>;
-  __shared__ AddSmem<N, M, T> sm;
-  const int lbr = xcd_block(((a.nel + Sh::EPB - 1) / Sh::EPB) * a.nrhs);
+  __shared__ AddSmem<N, M, T, EPB> sm;
+  const int lbr = xcd_block(((a.nel + EPB - 1) / EPB) * a.nrhs);
   if (lbr < 0) return;
-  overlap_add_tile<N, M, T>(a, lbr, sm);
+  overlap_add_tile<N, M, T, EPB>(a, lbr, sm);
 }
 
 // ---------------------------------------------------------------------------
@@ -876,12 +877,19 @@ void launch_schwarz(const SchwarzArgs<T>& a, hipStream_t st) {
   }
 }
 
+template <int N, int M, typename T, int EPB>
+void launch_overlap_tiles(const SchwarzArgs<T>& a, hipStream_t st) {
+  const int nb = ((a.nel + EPB - 1) / EPB) * a.nrhs;
+  hipLaunchKernelGGL((schwarz_overlap_add_kernel<N, M, T, EPB>), dim3(xcd_grid(nb)), dim3(AddShape<N, EPB>::THREADS), 0, st,
+                     a);
+}
 template <int N, int M, typename T>
 void launch_overlap(const SchwarzArgs<T>& a, hipStream_t st) {
   if constexpr (M > 0) {
-    using Sh = AddShape<N>;
-    const int nb = ((a.nel + Sh::EPB - 1) / Sh::EPB) * a.nrhs;
-    hipLaunchKernelGGL((schwarz_overlap_add_kernel<N, M, T>), dim3(xcd_grid(nb)), dim3(Sh::THREADS), 0, st, a);
+    if constexpr (add_elems(N, 0) != kAddElems[N]) {   // one element a tile on few elements
+      if (add_elems(N, a.nel) == 1) return launch_overlap_tiles<N, M, T, 1>(a, st);
+    }
+    launch_overlap_tiles<N, M, T, kAddElems[N]>(a, st);
   }
 }
 
@@ -996,7 +1004,7 @@ constexpr size_t add_smem_upto() {
 }
 
 template <int NMAX, typename T, bool PERSIST>
-__global__ void __launch_bounds__(AddShape<NMAX>::THREADS)
+__global__ void __launch_bounds__((AddShape<NMAX, 1>::THREADS))
 overlap_add_batched_kernel(SchwarzArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, int ntiles) {
   __shared__ __align__(16) char smem[add_smem_upto<T, NMAX>()];
   // tiles dealt round-robin over the XCDs (the hardware order), strided in the persistent form
@@ -1014,7 +1022,7 @@ overlap_add_batched_kernel(SchwarzArgs<T> a, const BucketDesc<T>* __restrict__ b
     switch (bd[k].p) {
 #define DGFAS_ADB(P)                                                          \
   case P:                                                                     \
-    if constexpr (P + 1 <= NMAX) overlap_add_tile<P + 1, 1, T>(x, lbr, *reinterpret_cast<AddSmem<P + 1, 1, T>*>(smem), tid); \
+    if constexpr (P + 1 <= NMAX) overlap_add_tile<P + 1, 1, T, kAddElems[P + 1]>(x, lbr, *reinterpret_cast<AddSmem<P + 1, 1, T>*>(smem), tid); \
     break;
       DGFAS_ADB(1) DGFAS_ADB(2) DGFAS_ADB(3) DGFAS_ADB(4) DGFAS_ADB(5) DGFAS_ADB(6) DGFAS_ADB(7) DGFAS_ADB(8)
 #undef DGFAS_ADB

@@ -65,9 +65,18 @@ struct BatchLaunch {
   bool persistent = false;   // fewer workgroups than tiles: each strides through the list
 };
 enum { kStageOp = 0, kStageSolve = 1, kStageAdd = 2 };
-// elements per 256-thread tile of the overlap add by n = p + 1: two to four nodes a thread, so that
-// a tile's loads overlap and its dot products are reduced once for that many nodes
+// elements per 256-thread tile of the overlap add by n = p + 1: one node a thread up to n = 5, three or four
+// from n = 6 on, so that a tile's loads overlap and its dot products are reduced once for that many
+// nodes.  A launch per degree on fewer than kAddFull elements takes one element a tile from n = 6 on: there the
+// chip is not full and the longer tile is only a longer chain.  One element a tile and these, FP64 (FP32):
+// p = 5: 8^3 3.7, 6.4 us   16^3 9.4, 9.8 (8.5, 9.0)   20^3 14.8, 15.4 (13.4, 11.9)   27^3 33.6, 31.1 (29.2, 25.5)
+// p = 6: 8^3 4.3, 5.2   20^3 20.8, 20.6   27^3 47.0, 44.1
+// p = 7: 8^3 4.5, 6.0   20^3 26.0, 27.3 (19.3, 20.4)   32^3 118.7, 122.8 (72.7, 70.7)
+// The line counts elements, not elements times right-hand sides: the fused dot products of a right-hand side
+// are then summed in the same order alone and in a batch.
 constexpr int kAddElems[10] = {0, 0, 32, 9, 4, 2, 4, 2, 2, 1};
+constexpr int kAddFull = 6144;
+constexpr int add_elems(int n, int nel) { return n >= 6 && nel < kAddFull ? 1 : kAddElems[n]; }
 // tiles per bucket of each stage (element blocks times right-hand sides); pmax: largest degree of the
 // batched launch (subdomain solves only)
 int stage_tiles(int stage, int p, int nel, int nrhs, int pmax = 8);

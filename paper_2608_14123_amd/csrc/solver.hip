@@ -1495,7 +1495,8 @@ void build_level(Solver& s, Level& L, const std::vector<int>& deg, const double*
     L.nlb = stage_tiles(kStageOp, L.p, nsweep, 1);
     s.reserve(L.kpart, (size_t)L.nlb * s.nrhs);
     if (L.m > 0 && !L.topo) {
-      L.nla = stage_tiles(kStageAdd, L.p, nsweep, 1);
+      const int epb = add_elems(L.p + 1, nsweep);
+      L.nla = (nsweep + epb - 1) / epb;
       s.reserve(L.zpart, (size_t)2 * L.nla * s.nrhs);
     }
   }
