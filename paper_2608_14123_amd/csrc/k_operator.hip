@@ -505,7 +505,8 @@ sipg_batched_kernel(OpArgs<T> a, const BucketDesc<T>* __restrict__ bd, int nb, i
   // the large tiles.  The persistent form (fewer workgroups than tiles) strides through the
   // list, with a barrier between tiles for the shared memory.  It takes the thread index
   // through an opaque register copy in every tile, so that no degree branch's index arithmetic
-  // is hoisted above the loop and kept live across it (that cost 48 VGPRs and scratch).
+  // is hoisted above the loop and kept live across it.  Constants of the branches still are: at p = 8
+  // in FP64 it takes 159 registers, the one-tile form 136, three waves per SIMD both.
   auto tile = [&](int t) {
     int tid = threadIdx.x;
     if constexpr (PERSIST) asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"(tid));

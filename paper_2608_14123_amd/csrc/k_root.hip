@@ -4,9 +4,10 @@
 // On such a level every kernel of the general solve is far below one wave of the chip, and an
 // iteration is a chain of eight launches whose 2 to 5 us each are launch and drain latency: the
 // 4^3 root of the unit-cube p = 4 hierarchy (about 20 iterations to 1e-12, seven cycles a solve) took
-// nine tenths of the solve.  Here the vectors stay in registers (one thread per node), what other
-// threads read goes through LDS, and an iteration is five workgroup barriers: 8 us, and the whole
-// solve went from 7.4 to 2.7 ms.
+// nine tenths of the solve.  Here a thread keeps its node's vector entries from iteration to iteration, what
+// other threads read goes through LDS, and an iteration is five workgroup barriers: 8 us, and the whole
+// solve went from 7.4 to 2.6 ms, of which these launches are still nearly half.  1024 threads leave each 128
+// registers; 54 values that it holds over the loop (indices, destinations, weights) are in scratch memory.
 // The steps are those of the general kernels: gather, fast-diagonalisation solve and weighted
 // scatter per subdomain (sixteen threads, one xi_3 column each; the exchanges stay inside a
 // wavefront), the inbox sum per node, the SIPG operator from the node's own element and its three face

@@ -75,8 +75,9 @@ void Mlp::reserve(int rows) {
   cap = rows;
 }
 
-// a training batch's outputs, kept until a larger batch or the network's end: an allocation a call
-// cost more than a third of a gradient of 4096 rows (299 us with it, 191 without, the loss copied to page-locked memory)
+// a training batch's outputs, kept until a larger batch or the network's end (22 MB at 4096 x 1331): an
+// allocation a call cost more than a third of a repeated gradient of 4096 rows (299 us with it, 191 without,
+// the loss copied to page-locked memory).  A network's first gradient allocates them as before.
 float* Mlp::outputs(int rows) {
   if (rows > ycap) {
     MHIP(hipStreamSynchronize(st));

@@ -338,9 +338,10 @@ struct Solver {
   }
   // workgroups of a one-launch batch: one per tile, or a persistent grid that strides through
   // the tiles (a multiple of 8, so that the round-robin XCD order of the tiles is kept)
-  // A persistent launch keeps about 24 waves per CU: the workgroups per CU follow the stage's
-  // workgroup width at the level's largest degree (2 for the 768-thread operator tile at p = 8,
-  // 12 for the 2-wave subdomain solve, 6 for the 4-wave overlap add).
+  // A persistent launch has about 24 waves per CU: the workgroups per CU follow the stage's
+  // workgroup width at the level's largest degree (6 for the operator's and the overlap add's
+  // four waves, 12 or 24 for the subdomain solve's two or one).  The subdomain solve's registers let 24
+  // (FP64) or more reside; the operator's let 12 in FP64, the rest follows as workgroups end.
   int persistent_grid(int stage, int pmax) const {
     const int waves = std::max(1, stage_threads(stage, pmax) / 64);
     const int per_cu = std::max(1, 24 / waves);
