@@ -26,7 +26,7 @@ BF16_PEAK_TFLOPS = 2500.0     # dense BF16 matrix-core peak
 # HBM bytes of one residual launch of the operator kernel at 32^3, p = 7 from rocprofv3
 # FETCH_SIZE / WRITE_SIZE runs, scaled by a 1 GiB copy (profiles/c2_curved_p7_hbm_traffic_pmc.md);
 # valid only for the kernel source it was measured on.
-OPERATOR_TRAFFIC = {'sha256_prefix': 'c9cbd3c81174ade8', 'bytes': 1.686e9, 'ne': 32, 'p': 7}
+OPERATOR_TRAFFIC = {'sha256_prefix': '567f924fa2934f52', 'bytes': 1.683e9, 'ne': 32, 'p': 7}
 
 
 def parse():
