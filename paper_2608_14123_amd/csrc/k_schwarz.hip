@@ -607,8 +607,7 @@ __device__ __forceinline__ T inbox_sum(const T* box, const int* sOff, const int 
 
 // z[node] += sum of the neighbours' overlap contributions in the element's own inbox.  From n = 4 on the
 // inbox, one contiguous block, comes into LDS with coalesced loads: reading the up to 7 entries of
-// every node from global memory kept the address units busy 79 % of the launch (32^3, p = 7:
-// 128 us with seven loads a node, 104 from LDS with one node a thread, now 73; with the dot
+// every node from global memory is seven short gathers a node (32^3, p = 7: 128 us that way, 104 from LDS with one node a thread, now 73; with the dot
 // products 154, now 123, in FP32 122, now 71).  With dotz set, also the tile's sums of z dr and
 // z (dr - dr0) over every node (deterministic order).
 template <int N, int M, typename T, int EPB>
